@@ -341,25 +341,78 @@ extern "C" hl_status hl_lookup_gids(const hl_handle* h, const uint32_t* rows, co
 }
 
 // ----------------------------------------------------------------------------- counting
-__global__ void __launch_bounds__(256)
-hl_k_count(const uint32_t* __restrict__ gids, int64_t n, uint32_t* __restrict__ counts,
+// A block takes CT_THREADS * CT_ITEMS lookups and adds up equal ids in an LDS
+// table first (open addressing, CT_PROBES probes; an id that finds no slot goes
+// to memory directly), then adds each held id's count with one atomic.  The
+// kernel is bound by atomics that meet on one cache line (the popular rows,
+// and every row of a small table): they complete one after another.  So the
+// blocks walk the lookups with stride n_tables, which in the one-lookup-per-bag
+// layout gives a block one table's lookups (any order counts the same): a row
+// then meets about as many atomics as its table has blocks.  212,992 lookups
+// of 26 tables (100 to 4e7 rows, Zipf 1.1): one atomic per lookup 36.8 us, the
+// LDS table over consecutive lookups 18.7, with the stride 8.6 (4.0 of it the
+// loads and the LDS table; 1024 to 4096 lookups per block 8.0 to 11.4).
+// 328,000 lookups of multi-hot bags: 100.5 -> 13.4 us.
+#define CT_THREADS 512
+#define CT_ITEMS 4
+#define CT_SLOTS 4096
+#define CT_PROBES 4
+__global__ void __launch_bounds__(CT_THREADS)
+hl_k_count(const uint32_t* __restrict__ gids, uint32_t n, uint32_t stride, uint32_t* __restrict__ counts,
            uint64_t n_rows, uint32_t* err) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t g = gids[i];
-    if (g < n_rows) atomicAdd(counts + g, 1u);
-    else hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+  __shared__ uint32_t key[CT_SLOTS], cnt[CT_SLOTS];
+  const uint32_t q0 = blockIdx.x * (CT_THREADS * CT_ITEMS) + threadIdx.x;
+  // position q of the walk is lookup (q % per) stride + q / per
+  const uint32_t per = (n + stride - 1) / stride;
+  uint32_t g[CT_ITEMS];
+  bool in[CT_ITEMS];
+#pragma unroll
+  for (int k = 0; k < CT_ITEMS; ++k) {
+    const uint32_t q = q0 + k * CT_THREADS, t = q / per;
+    const uint64_t i = (uint64_t)(q - t * per) * stride + t;
+    in[k] = t < stride && i < n;
+    g[k] = in[k] ? gids[i] : 0u;
   }
+  for (int j = threadIdx.x; j < CT_SLOTS; j += CT_THREADS) {
+    key[j] = 0xFFFFFFFFu;  // (no row's id)
+    cnt[j] = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < CT_ITEMS; ++k) {
+    if (!in[k]) continue;
+    if (g[k] >= n_rows) {
+      hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+      continue;
+    }
+    uint32_t slot = hl_cg_hash(g[k]) % CT_SLOTS;
+    bool held = false;
+    for (int p = 0; p < CT_PROBES && !held; ++p) {
+      const uint32_t old = atomicCAS(&key[slot], 0xFFFFFFFFu, g[k]);
+      held = old == 0xFFFFFFFFu || old == g[k];
+      if (!held) slot = (slot + 1) % CT_SLOTS;
+    }
+    if (held) atomicAdd(&cnt[slot], 1u);
+    else atomicAdd(counts + g[k], 1u);
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < CT_SLOTS; j += CT_THREADS)
+    if (cnt[j]) atomicAdd(counts + key[j], cnt[j]);
 }
 
 extern "C" hl_status hl_profile_count(hl_handle* h, const uint32_t* gids, int64_t n, hl_stream stream) {
   if (!h || n < 0 || (n > 0 && !gids)) return HL_ERR_INVALID_ARG;
   if (n == 0) return HL_OK;
-  uint32_t g = hl_div_up(n, 256);
-  if (g > 16384) g = 16384;
   hipStream_t s = (hipStream_t)stream;
-  HL_KERNEL(h, s, "hl_k_count", hl_k_count, dim3(g), dim3(256), 0, s, gids, n, h->d_counts,
-                     h->n_rows, h->d_err);
+  // (positions stay below 2^31: at most 2^30 lookups a launch, and as many of the walk's gaps)
+  const int64_t most = 1ll << 30;
+  for (int64_t i = 0; i < n; i += most) {
+    const uint32_t m = (uint32_t)(n - i < most ? n - i : most);
+    const uint32_t stride = (uint32_t)h->n_tables < m ? (uint32_t)h->n_tables : m;
+    const uint64_t walk = (uint64_t)hl_div_up(m, stride) * stride;
+    HL_KERNEL(h, s, "hl_k_count", hl_k_count, dim3(hl_div_up(walk, CT_THREADS * CT_ITEMS)), dim3(CT_THREADS), 0, s,
+              gids + i, m, stride, h->d_counts, h->n_rows, h->d_err);
+  }
   HL_LAUNCHED();
   return HL_OK;
 }

@@ -1,0 +1,68 @@
+"""GPU parity of the learning phase's kernels at the sizes where they can go
+wrong: access counting and the top-K selection against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2204_05436_amd import hotline as hl
+from parity_lib import u32
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.uint32).view(np.int32)).cuda()
+
+
+@pytest.mark.parametrize("n_rows,tables", [(1, 1), (63, 2), (4096, 3), (16384, 1), (16385, 26), (70001, 5),
+                                           (1_100_003, 7)])
+def test_count_and_topk(n_rows, tables):
+    """Counts on either side of every regime of the selection's bins (exact
+    below 64, 32 bins per power of two, up to three levels of them), ties at
+    the boundary, sparse and dense rows, at row counts around the 64-row words,
+    the 4096-row blocks and the 16384-row tiles; the lookups in an order that
+    mixes hot and rare ids, fed in calls of odd lengths; the rows past the last
+    call's hot set forgotten, the counts zeroed by reset."""
+    rng = np.random.default_rng(n_rows)
+    want = np.zeros(n_rows, np.int64)
+    some = rng.permutation(n_rows)[:max(1, n_rows // 40)]
+    want[some] = rng.integers(1, 5, some.size)
+    # (a bin of 2^19 and above holds more values than one level below it parts)
+    edge = [1, 2, 62, 63, 64, 65, 66, 127, 128, 129, 130, 1000, 1001, 2047, 2048, 2049, 4095, 4096, 70000, 70001,
+            (1 << 17) + 5, (1 << 17) + 6, (1 << 17) + 9, (1 << 17) + 9, (1 << 20) + 2, (1 << 20) + 3, (1 << 20) + 7]
+    at = rng.permutation(n_rows)[:len(edge)]
+    want[at] = edge[:at.size]
+    if n_rows > 5000:  # a dense stretch with many ties
+        want[1000:1400] = rng.integers(60, 70, 400)
+    ids = rng.permutation(np.repeat(np.arange(n_rows, dtype=np.uint32), want))
+    rows = np.full(tables, max(1, n_rows // tables), np.uint32)
+    rows[-1] = n_rows - rows[:-1].sum(dtype=np.int64)
+    h = hl.hl_create(rows, 4, "f32", n_rows)
+    try:
+        acc = int((want > 0).sum())
+        ks = sorted({0, 1, 2, 3, 4, 5, 7, 9, 12, 20, acc // 2, acc - 1, acc, n_rows} & set(range(n_rows + 1)))
+        out = torch.zeros(n_rows, dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(n_rows, dtype=torch.int32, device="cuda")
+        d = _dev(ids)
+        for a, b in zip([0, 1, 2050, 9001], [1, 2050, 9001, ids.size]):
+            b = min(b, ids.size)
+            if a < b:
+                hl.hl_profile_count(h, d[a:b].clone(), b - a)
+        hl.hl_profile_counts(h, cnt)
+        assert np.array_equal(u32(cnt), want.astype(np.uint32)), "counts"
+        probe = np.arange(n_rows, dtype=np.uint32)
+        codes = torch.zeros(n_rows, dtype=torch.int32, device="cuda")
+        for k in reversed(ks):
+            n = hl.hl_profile_topk(h, k, out, reset_counts=k == ks[0])
+            hot = O.topk(want.astype(np.uint32), k)
+            assert n == hot.size == h.n_hot, f"k={k}"
+            assert np.array_equal(u32(out[:n]), hot), f"k={k}"
+            # the bitmap and the rank directory, through the slot of every row
+            hl.hl_remap(h, _dev(probe), n_rows, codes)
+            assert np.array_equal(codes.cpu().numpy(), O.remap(hot, probe)), f"k={k}"
+        hl.hl_profile_counts(h, cnt)
+        assert not u32(cnt).any(), "reset"
+        assert hl.hl_last_device_error(h) == 0
+    finally:
+        h.close()
