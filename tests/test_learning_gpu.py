@@ -66,3 +66,32 @@ def test_count_and_topk(n_rows, tables):
         assert hl.hl_last_device_error(h) == 0
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("n_sets,ways,n", [(1, 16, 7), (1, 16, 8), (1, 5, 9), (1, 16, 71), (2, 1, 81), (1, 16, 72),
+                                           (1, 16, 137), (3, 16, 5000), (7, 3, 9000), (40, 16, 20011), (300, 2, 3000)])
+def test_logger_long_runs(n_sets, ways, n):
+    """The access logger's replay of runs around the lengths where it changes
+    form (8 accesses by one thread, then 64 at a time by a wave): few sets, so
+    that every batch gives each a long run; ids from all hits to all misses;
+    every entry against the oracle after each batch."""
+    rng = np.random.default_rng(n * 31 + ways)
+    h = hl.hl_create(np.array([1 << 20], np.uint32), 4, "f32", 16)
+    e, oe = hl.EAL(h, n_sets, ways, n), O.EAL(n_sets, ways)
+    tags = torch.zeros(n_sets * ways, dtype=torch.int32, device="cuda")
+    rr = torch.zeros(n_sets * ways, dtype=torch.uint8, device="cuda")
+    try:
+        for b, spread in enumerate([n_sets * ways // 2 + 1, 2 * n_sets * ways + 3, 1 << 20, n_sets * ways + 1, 1]):
+            g = rng.integers(0, spread, n).astype(np.uint32)
+            hot = rng.random(n) < 0.6  # a few ids that keep hitting among the rest
+            g[hot] = rng.integers(0, max(1, n_sets * ways // 3), int(hot.sum()))
+            g[rng.random(n) < 0.02] = np.uint32(0xFFFFFFFF)  # not logged
+            hl.hl_eal_access(e, _dev(g), n)
+            oe.access(g)
+            hl.hl_eal_state(e, tags, rr)
+            torch.cuda.synchronize()
+            assert np.array_equal(u32(tags), oe.tag), f"batch {b}: ids"
+            assert np.array_equal(rr.cpu().numpy(), oe.rrpv), f"batch {b}: values"
+    finally:
+        e.close()
+        h.close()
