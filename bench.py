@@ -61,8 +61,7 @@ def kernel_bytes(name, st, alone=False):
             "gt_sort": 12 * L,
             # the forward and the tables' sorts in one launch
             "eb_fwd_gt": 4 * L + 4 * (nb + 1) + U * R + nb * O + 12 * L,
-            "bw_prep_hist": 4 * L + 4 * (nb + 1) + 8 * L,
-            "srt_hist": 4 * L,
+            "srt_count": 4 * L,
             "srt_pass": 16 * L,
             # reduction: sorted keys and bags, dY, each updated row read and written
             "bw_reduce1": 8 * L + nb * O + 2 * U * R,
@@ -76,12 +75,11 @@ def kernel_bytes(name, st, alone=False):
         "cg_codes": 8 * Lc + 4 * C,
         # the host-link copy (also reported against the link's peak)
         "cg_fetch": 4 * C + 2 * C * R,
-        # grouping: keys and bags out (with the fused plan's cold codes: a slot
-        # read and a code written per cold lookup), a histogram read, the
-        # pairs in and out per pass
+        # grouping: keys and bags out; the codes in (with the fused plan's cold
+        # codes: a slot read and a code written per cold lookup); the pairs in
+        # and out per pass
         "bw_prep": 4 * L + 4 * (nb + 1) + 8 * L,
-        "srt_hist": 4 * L,
-        "bw_prep_hist": 4 * L + 4 * (nb + 1) + 8 * L + 8 * Lc,
+        "srt_count": 4 * L + 8 * Lc,
         "srt_pass": 16 * L,
         "gt_prep": 4 * L + 4 * (nb + 1) + 4 * L + 8 * Lc,
         "gt_sort": 12 * L,
@@ -432,8 +430,8 @@ def main():
 
     # the embedding forward and backward: their kernels' time per step (the
     # grouping included), against the algorithmic bytes of both passes
-    fb_kernels = ("eb_fwd", "eb_fwd_gt", "eb_fwd_hot", "eb_fwd_tail", "eb_tail_r2", "eb_bags_r2", "bw_prep", "bw_prep_hist",
-                  "srt_hist", "srt_pass", "gt_prep", "gt_sort", "bw_reduce1", "bw_reduce2", "bw_cold")
+    fb_kernels = ("eb_fwd", "eb_fwd_gt", "eb_fwd_hot", "eb_fwd_tail", "eb_tail_r2", "eb_bags_r2", "bw_prep",
+                  "srt_count", "srt_pass", "gt_prep", "gt_sort", "bw_reduce1", "bw_reduce2", "bw_cold")
     t_fb = sum(kernels[n]["ms_per_step"] for n in fb_kernels if n in kernels)
     t_fb_alone = sum(kernels_alone[n]["ms_per_step"] for n in fb_kernels if n in kernels_alone)
     fwd_b = 4 * avg["L"] + 4 * (avg["n_bags"] + 1) + avg["U"] * avg["R"] + avg["n_bags"] * avg["O"]

@@ -747,41 +747,6 @@ __device__ __forceinline__ void bw_uncovered(const int32_t* bag_ptr, int64_t n_b
 }
 
 
-// the bags [b0, b0 + nb) of one block: off[] holds their offsets.  The fused
-// plan (cf.table) also writes the cold lookups' codes and frees their slots,
-// as the cold plan's last kernel does.
-template <int NT>
-__device__ __forceinline__ void bw_prep_bags(int32_t* codes, const int32_t* off, int64_t b0, int nb, int32_t bps,
-                                             const uint8_t* __restrict__ mask, uint32_t n_hot, uint32_t k_cap,
-                                             int32_t stg_rows, uint32_t* __restrict__ keys,
-                                             uint32_t* __restrict__ vals, int64_t n_lookups, uint32_t* err,
-                                             const hl_cg_fused& cf, bool fits) {
-  const int32_t lo = off[0], hi = min((int64_t)off[nb], n_lookups);
-  for (int32_t i = lo + threadIdx.x; i < hi; i += NT) {
-    int a = 0, b = nb;
-    while (b - a > 1) {
-      int m = (a + b) >> 1;
-      if (off[m] <= i) a = m; else b = m;
-    }
-    const int64_t bag = b0 + a;
-    uint32_t key = EB_SENT;
-    if (!mask || mask[bag / bps]) {
-      int32_t c = codes[i];
-      if (cf.table && c == -1) {
-        const uint32_t sl = cf.slotof[i];
-        c = bw_fused_code(c, (uint32_t)i, cf, k_cap, fits);
-        if (c != -1) codes[i] = c;
-        if (sl < cf.S) cf.table[sl] = 0;
-      }
-      key = bw_key((uint32_t)c, n_hot, k_cap, stg_rows);
-      if (key == EB_SENT) hl_flag(err, HL_DEVERR_BAD_CODE);
-    }
-    keys[i] = key;
-    vals[i] = (uint32_t)bag;
-  }
-}
-
-
 #define BP_BAGS 256
 __global__ void __launch_bounds__(256)
 bw_prep(const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr, int64_t n_bags, int32_t bps,
@@ -800,76 +765,22 @@ bw_prep(const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr, 
   const int64_t gs = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int64_t i = t0; i < first; i += gs) keys[i] = EB_SENT;
   for (int64_t i = covered + t0; i < n_lookups; i += gs) keys[i] = EB_SENT;
-  bw_prep_bags<256>(const_cast<int32_t*>(codes), off, b0, nb, bps, mask, n_hot, k_cap, stg_rows, keys, vals,
-                    n_lookups, err, hl_cg_fused{}, false);
-}
-
-// bw_prep and the sort's digit histogram in one launch (no sample selection):
-// blocks [0, hb) count the digits of every key, taking the keys from the codes
-// by the same rule as the writers, and clear the first pass's status words;
-// the other blocks write the (key, bag) pairs, bpb bags each (at most
-// BPH_BAGS: fewer when bags hold many lookups, so the writers spread over
-// the chip).  In the
-// fused plan (cf.table) both roles take a cold lookup's code from the cold
-// plan's state (the writers also store it; a reader that meets the stored
-// code derives the same key), and the first writer block reports rows that do
-// not fit the staging buffer.
-#define BPH_THREADS 1024
-#define BPH_BAGS 1024
-template <int NB>
-__global__ void __launch_bounds__(BPH_THREADS)
-bw_prep_hist(int32_t* codes, const int32_t* __restrict__ bag_ptr, int64_t n_bags, int32_t bps, uint32_t n_hot,
-             uint32_t k_cap, int32_t stg_rows, uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-             int64_t n_lookups, uint32_t hb, int passes, int b, uint32_t* __restrict__ part,
-             uint32_t* __restrict__ zero, uint64_t n_zero, int32_t bpb, uint32_t* sflag, uint32_t sv, uint32_t* err,
-             hl_cg_fused cf) {
-  __shared__ uint32_t hst[HL_SORT_MAXPASS][NB];
-  __shared__ int32_t off[BPH_BAGS + 1];
-  bw_start_signal(sflag, sv);
-  int64_t first, covered;
-  bw_uncovered(bag_ptr, n_bags, n_lookups, &first, &covered);
-  const bool fits = cf.table && *cf.ncold <= (uint32_t)cf.cap;
-  if (blockIdx.x < hb) {
-    const uint32_t gs = hb * BPH_THREADS;
-    for (uint64_t i = (uint64_t)blockIdx.x * BPH_THREADS + threadIdx.x; i < n_zero; i += gs) zero[i] = 0;
-    for (int j = threadIdx.x; j < HL_SORT_MAXPASS * NB; j += BPH_THREADS) (&hst[0][0])[j] = 0;
-    __syncthreads();
-    const uint32_t mask = (1u << b) - 1u;
-    const uint32_t n = (uint32_t)n_lookups;
-    for (uint32_t i0 = blockIdx.x * BPH_THREADS + threadIdx.x; i0 < n; i0 += 8 * gs) {
-      uint32_t k[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t i = i0 + u * gs;
-        k[u] = i < n ? (uint32_t)codes[i] : 0u;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t i = i0 + u * gs;
-        if (i >= n) continue;
-        const uint32_t c = (uint32_t)bw_fused_code((int32_t)k[u], i, cf, k_cap, fits);
-        const uint32_t key = (int64_t)i < first || (int64_t)i >= covered ? EB_SENT : bw_key(c, n_hot, k_cap, stg_rows);
-        for (int p = 0; p < passes; ++p) atomicAdd(&hst[p][(key >> (b * p)) & mask], 1u);
-      }
+  const int32_t lo = off[0], hi = min((int64_t)off[nb], n_lookups);
+  for (int32_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
+    int a = 0, b = nb;
+    while (b - a > 1) {
+      int m = (a + b) >> 1;
+      if (off[m] <= i) a = m; else b = m;
     }
-    __syncthreads();
-    for (int p = 0; p < passes; ++p)
-      for (int j = threadIdx.x; j < NB; j += BPH_THREADS)
-        part[((size_t)p * HL_SORT_HIST_BLOCKS + blockIdx.x) * NB + j] = hst[p][j];
-    return;
+    const int64_t bag = b0 + a;
+    uint32_t key = EB_SENT;
+    if (mask[bag / bps]) {
+      key = bw_key((uint32_t)codes[i], n_hot, k_cap, stg_rows);
+      if (key == EB_SENT) hl_flag(err, HL_DEVERR_BAD_CODE);
+    }
+    keys[i] = key;
+    vals[i] = (uint32_t)bag;
   }
-  const uint32_t blk = blockIdx.x - hb;
-  const int64_t b0 = (int64_t)blk * bpb;
-  const int nb = (int)min((int64_t)bpb, n_bags - b0);
-  for (int j = threadIdx.x; j <= nb; j += BPH_THREADS) off[j] = bag_ptr[b0 + j];
-  if (blk == 0 && threadIdx.x == 0 && bag_ptr[n_bags] != n_lookups) hl_flag(err, HL_DEVERR_SHAPE);
-  if (blk == 0 && threadIdx.x == 0 && cf.table && !fits) hl_flag(err, HL_DEVERR_CAPACITY);
-  __syncthreads();
-  const int64_t gs = (int64_t)(gridDim.x - hb) * BPH_THREADS, t0 = (int64_t)blk * BPH_THREADS + threadIdx.x;
-  for (int64_t i = t0; i < first; i += gs) keys[i] = EB_SENT;
-  for (int64_t i = covered + t0; i < n_lookups; i += gs) keys[i] = EB_SENT;
-  bw_prep_bags<BPH_THREADS>(codes, off, b0, nb, bps, nullptr, n_hot, k_cap, stg_rows, keys, vals, n_lookups, err, cf,
-                            fits);
 }
 
 template <int VEC, bool BF>
@@ -1590,23 +1501,18 @@ hl_status hl_embbag_bwd_plan_signal(hl_handle* h, int32_t stg_rows, int32_t* cod
                            cf && cf->table ? cf : nullptr, s);
     *sent = sflag != nullptr;
   } else {
-    if ((uint64_t)n_lookups > ws.sort.n_max) return HL_ERR_CAPACITY;
-    const hl_sort_geom sg = hl_sort_geometry((uint32_t)n_lookups, bits, hl_stream_cus(s));
-    // bags per writer block: up to about 8192 lookups each, 64 to BPH_BAGS bags
-    int32_t bpb = BPH_BAGS;
-    while (bpb > 64 && (int64_t)bpb * n_lookups > 8192 * n_bags) bpb >>= 1;
-    const dim3 grid(sg.hist_blocks + (uint32_t)hl_div_up(n_bags, bpb));
-#define BPH(NB)                                                                                                  \
-  HL_KERNEL(h, s, "bw_prep_hist", bw_prep_hist<NB>, grid, dim3(BPH_THREADS), 0, s, codes, bag_ptr, n_bags, bps, h->n_hot, \
-            h->k_cap, stg_rows, ws.sort.k0, ws.sort.v0, n_lookups, sg.hist_blocks, sg.passes, sg.b, ws.sort.part,   \
-            ws.sort.st[0], sg.n_zero, bpb, sflag, sval, h->d_err, cf ? *cf : hl_cg_fused{})
-    if (sg.nb == 256) BPH(256);
-    else if (sg.nb == 1024) BPH(1024);
-    else BPH(2048);
-#undef BPH
-    HL_LAUNCHED();
-    *sent = sflag != nullptr;
-    st = hl_sort_passes(h, ws.sort, nullptr, (uint32_t)n_lookups, bits, s, &sk, &sv);
+    hl_sort_src src{};
+    src.codes = codes;
+    src.bag_ptr = bag_ptr;
+    src.n_bags = n_bags;
+    src.n_hot = h->n_hot;
+    src.k_cap = h->k_cap;
+    src.stg_rows = stg_rows;
+    src.sflag = sflag;
+    src.sv = sval;
+    if (cf) src.cf = *cf;
+    st = hl_sort_codes(h, ws.sort, src, (uint32_t)n_lookups, bits, s, &sk, &sv);
+    *sent = st == HL_OK && sflag != nullptr;
   }
   if (st != HL_OK) return st;
   hl_ws_note(h, workspace, HL_WSK_BWD_PLAN, n_lookups, n_bags, stg_rows);

@@ -148,13 +148,15 @@ __device__ __forceinline__ void hl_flag(uint32_t* err, uint32_t bit) { atomicOr(
 // lanes where `valid` holds (0 on a lane where it does not): one ballot per
 // digit bit, each keeping the lanes that agree on that bit.
 __device__ __forceinline__ uint64_t hl_match_digit(uint32_t digit, int bits, bool valid) {
-  uint64_t m = __ballot(valid);
+  const uint64_t all = __ballot(valid);
+  uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
   for (int b = 0; b < bits; ++b) {
-    const bool one = (digit >> b) & 1u;
-    const uint64_t ones = __ballot(one);
-    m &= one ? ones : ~ones;
+    const uint32_t t = (uint32_t)((int32_t)(digit << (31 - b)) >> 31);  // the bit, on every bit
+    const uint64_t ones = __ballot(t != 0);
+    lo &= ~((uint32_t)ones ^ t);
+    hi &= ~((uint32_t)(ones >> 32) ^ t);
   }
-  return valid ? m : 0ull;
+  return valid ? ((uint64_t)hi << 32) | lo : 0ull;
 }
 
 // ----------------------------------------------------------------------------- hot set probes
@@ -364,24 +366,28 @@ hl_status hl_group_by_table(hl_handle* h, int32_t* codes, const int32_t* bag_ptr
 
 // ----------------------------------------------------------------------------- sort
 // Stable LSD radix sort of (key, value) uint32 pairs with digits of up to 11
-// bits: one histogram kernel plus one kernel per digit with decoupled look-back
-// for the cross-tile digit offsets.  See hl_sort.hip.
-#define HL_SORT_THREADS 512
+// bits: one launch that counts the tiles' digits, then one per digit.  See
+// hl_sort.hip.
+#define HL_SORT_THREADS 1024
 #define HL_SORT_WAVES (HL_SORT_THREADS / 64)
-// items per thread of a pass block: 4, 6 or 12 (the fewest that keep the
+// items per thread of a pass block: 1, 2, 4 or 8 (the fewest that keep the
 // tiles to HL_SORT_TILES_AIM and to the stream's compute units, so a small
 // sort still spreads over the units it has, in one round of blocks)
-#define HL_SORT_TILE_MIN (HL_SORT_THREADS * 4)
-#define HL_SORT_TILE_MAX (HL_SORT_THREADS * 12)
+#define HL_SORT_TILE_MIN HL_SORT_THREADS
+#define HL_SORT_TILE_MAX (HL_SORT_THREADS * 8)
 #define HL_SORT_TILES_AIM 128
+#define HL_SORT_GRP 8             // tiles whose counts are published together as well
 #define HL_SORT_MAXNB 2048        // bins of an 11-bit digit
 #define HL_SORT_MAXPASS 3
-#define HL_SORT_HIST_BLOCKS 16
-#define HL_SORT_HIST_THREADS 1024
 struct hl_sort_ws {
   uint32_t *k0, *v0, *k1, *v1;  // ping-pong buffers, n_max each; input in k0/v0
-  uint32_t* part;               // [HL_SORT_MAXPASS][HL_SORT_HIST_BLOCKS][HL_SORT_MAXNB] per-block digit counts
-  uint32_t* st[2];              // [tiles_max][HL_SORT_MAXNB] look-back status, alternating between passes
+  uint32_t* tot;                // [HL_SORT_MAXPASS][HL_SORT_MAXNB] digit totals of the passes after the first
+  uint32_t* row[4];             // [tiles_max][HL_SORT_MAXNB / 2] the tiles' digit counts: of the first pass
+                                // (later the third's published ones), of the second, the second's published
+                                // ones, of the third
+  uint64_t* grp[2];             // [ceil(tiles_max / HL_SORT_GRP)][HL_SORT_MAXNB / 2] published digit counts of
+                                // groups of tiles: of the second pass; of the third (and the first's prefixes)
+  uint64_t* gtot;               // [HL_SORT_MAXNB / 2] published digit totals of the first pass
   uint32_t* ctr;                // [8] self-resetting tile counters (in the workspace header)
   uint32_t tiles_max;
   uint32_t n_max;
@@ -397,28 +403,26 @@ hl_status hl_sort_pairs(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uin
 // The buffers hl_sort_pairs leaves its result in for a sort of `bits` bits
 // with n_host > 0.
 void hl_sort_result(const hl_sort_ws& ws, int bits, uint32_t** out_k, uint32_t** out_v);
-// A producer of the keys may count their digits itself (in the same launch
-// that writes them) and then run only the digit passes.  Geometry of a sort
-// of n_host items and `bits` bits: `passes` digits of `b` bits, nb bins,
-// hist_blocks partial counts per pass (ws.part[(p * HL_SORT_HIST_BLOCKS +
-// block) * nb + digit], digit p = (key >> (b * p)) & ((1 << b) - 1)), and the
-// first pass's status words ws.st[0][0 .. n_zero) to clear.
-struct hl_sort_geom {
-  int passes, b, nb;
-  int items;      // per thread of a pass block
-  uint32_t tile;  // items per pass block
-  uint32_t hist_blocks;
-  uint64_t n_zero;
+// What the first launches of a sort read: pairs (k, the sort's k0/v0), or the
+// slot codes of a mini-batch's lookups, whose pairs are (bw_key of the code,
+// bag).  From codes, the first launch also does what the fused plan's last
+// kernel would (cf.table), stores sv to *sflag as it starts, and sets
+// HL_DEVERR_SHAPE / BAD_CODE / CAPACITY.
+struct hl_sort_src {
+  const uint32_t* k;
+  int32_t* codes;        // NULL: pairs
+  const int32_t* bag_ptr;
+  int64_t n_bags;
+  uint32_t n_hot, k_cap;
+  int32_t stg_rows;
+  uint32_t* sflag;
+  uint32_t sv;
+  hl_cg_fused cf;
 };
-// cus: compute units of the stream the sort runs on (its mask; 0: unknown),
-// which cap the tiles (one pass block per unit)
-hl_sort_geom hl_sort_geometry(uint32_t n_host, int bits, int cus);
+hl_status hl_sort_codes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int bits, hipStream_t s,
+                        uint32_t** out_k, uint32_t** out_v);
 // Compute units in a stream's mask (0 if it cannot be read).
 int hl_stream_cus(hipStream_t s);
-// The digit passes of hl_sort_pairs, once the counts and the cleared status
-// words are in place (hl_sort_geometry); same contract otherwise.
-hl_status hl_sort_passes(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uint32_t n_host, int bits,
-                         hipStream_t s, uint32_t** out_k, uint32_t** out_v);
 
 // Decoupled look-back helpers (epoch-tagged 64-bit status words).  A status
 // word carries its own value, so relaxed agent-scope atomics suffice: no other

@@ -1,46 +1,69 @@
-// Stable LSD radix sort of (key, value) uint32 pairs.
+// Stable LSD radix sort of (key, value) uint32 pairs, or of the backward's
+// (key, bag) pairs read from the slot codes.
 //
 // A sort of `bits` bits takes P = ceil(bits / 11) passes of b = ceil(bits / P)
-// bits (two passes of 10 bits for the backward's 20-bit keys).  One histogram
-// kernel counts every digit position in a single read of the keys (per-block
-// counts) and clears the first pass's status words.  Then one kernel per
-// digit: a block takes the next tile (dynamic tile ids, so every lower tile is
-// already running), ranks its items by digit with per-wave LDS counters that
-// the lanes of one digit advance together (their peer mask found by ballots;
-// the counters' totals are the tile's digit counts), publishes the counts, adds up
-// the counts of all earlier tiles (read together, 64 words in flight per
-// thread: at these sizes every tile runs at once, so one round of loads
-// replaces a chain of inclusive prefixes), adds each digit's global offset
-// (the histogram's exclusive scan, which every tile forms), and writes out the
-// tile, which it has reordered in LDS (before reading the earlier tiles'
-// counts) so that each digit's run is contiguous.  Each pass
-// block also clears its tile's status words for the next pass.  Item order inside a tile
-// is wave-major, then item, then lane, which is index order, so the sort is
-// stable.
+// bits (two passes of 10 bits for 20-bit keys), in P + 1 launches over the same
+// tiles of consecutive items:
+//
+//   srt_count -- each tile's digit counts of every pass in one read of the keys
+//                (from slot codes: it forms them, points the fused plan's cold
+//                codes at their staging rows, and nothing is written per item).
+//   srt_pass  -- one per digit.  A block ranks its tile's items by digit with
+//                per-wave LDS counters that the lanes of one digit advance
+//                together (their peer mask found by ballots), reorders the tile
+//                in LDS so that each digit's run is contiguous, and writes the
+//                runs at their global offsets: the digit's offset (exclusive
+//                scan of its total over all tiles) plus the digit's count in the
+//                earlier tiles.  The first pass's tiles are srt_count's: a few
+//                blocks of its launch (the first by ticket, which wait for
+//                nothing) add up the counts and publish the totals and each
+//                group of 8 tiles' prefix, which a tile needs only once it has
+//                ranked its items.  A later pass's tiles hold other items: each
+//                publishes its counts, the last tile of a group the group's, and
+//                a tile reads its group's earlier tiles and the earlier groups,
+//                two rounds of loads (a chain of inclusive prefixes, or a read of
+//                every earlier tile's counts, takes rounds that grow with the
+//                tiles).  Tiles come from a ticket, so every lower one is already
+//                running.
+//
+// Item order inside a tile is wave-major, then item, then lane, which is index
+// order, so the sort is stable.  A pass is bound by latency (its dependent
+// phases; a tile's bytes take a microsecond): at 328,000 pairs and 10-bit
+// digits, 81 tiles of 4096, a later pass's are the ticket 1.0, loads and ranking
+// 3.1, offsets 1.6, LDS reorder 0.4, earlier counts 2.2, scatter 0.8 us.  With
+// 16 histogram blocks before the passes, 512-thread tiles and every earlier
+// tile's counts read, the three launches took 9.5 + 19.2 + 19.2 us; now 4.9 +
+// 13.3 + 11.2 (852,000 pairs, 11-bit digits: 19.3 + 34.7 + 34.7, now 6.4 + 23.6 +
+// 17.6; 64,500 pairs, 9-bit: 6.6 + 11.6 + 11.6, now 3.5 + 7.5 + 7.6).
+#include <algorithm>
+#include <utility>
+
 #include "hl_internal.h"
 
 void hl_sort_ws_carve(hl_carver& c, hl_sort_ws& ws, uint32_t n_max) {
   ws.n_max = n_max;
-  ws.tiles_max = n_max ? hl_div_up(n_max, HL_SORT_TILE_MIN) : 1;
+  // (fewer items per thread than 8 only up to HL_SORT_TILES_AIM tiles)
+  ws.tiles_max = std::max({std::min(hl_div_up(n_max, HL_SORT_TILE_MIN), (uint32_t)HL_SORT_TILES_AIM),
+                           hl_div_up(n_max, HL_SORT_TILE_MAX), 1u});
   ws.k0 = c.take<uint32_t>(n_max);
   ws.v0 = c.take<uint32_t>(n_max);
   ws.k1 = c.take<uint32_t>(n_max);
   ws.v1 = c.take<uint32_t>(n_max);
-  ws.part = c.take<uint32_t>((size_t)HL_SORT_MAXPASS * HL_SORT_HIST_BLOCKS * HL_SORT_MAXNB);
-  ws.st[0] = c.take<uint32_t>((size_t)ws.tiles_max * HL_SORT_MAXNB);
-  ws.st[1] = c.take<uint32_t>((size_t)ws.tiles_max * HL_SORT_MAXNB);
+  ws.tot = c.take<uint32_t>((size_t)HL_SORT_MAXPASS * HL_SORT_MAXNB);
+  for (int i = 0; i < 4; ++i) ws.row[i] = c.take<uint32_t>((size_t)ws.tiles_max * (HL_SORT_MAXNB / 2));
+  for (int i = 0; i < 2; ++i)
+    ws.grp[i] = c.take<uint64_t>((size_t)hl_div_up(ws.tiles_max, HL_SORT_GRP) * (HL_SORT_MAXNB / 2));
+  ws.gtot = c.take<uint64_t>(HL_SORT_MAXNB / 2);
   ws.ctr = c.base ? c.header() + HL_HDR_SORT : nullptr;
 }
 
-// Status of (tile, digit): a flag bit (0 = not yet published) over the
-// tile's count of the digit.  With one digit per owning thread a 32-bit word
-// per digit (SRT_AGG); with two or more, two digits share a word, 16 bits
-// each (SRT_AGG2 per half: a tile's count stays below 2^15), so a thread
-// reads its digits' counts of a tile in one load.  Relaxed agent-scope
-// atomics: a word carries its own value and no other data is published
-// through it.
-#define SRT_AGG 0x40000000u
-#define SRT_VAL 0x3FFFFFFFu
+// Published counts of a group of tiles: two digits in a 64-bit word
+// (hl_st_store, hl_st_load), bit 31 of each half telling that it is there.
+#define SRT_GRP2 0x8000000080000000ull
+// A tile's counts take one 32-bit word per two digits, 15 bits each (a tile has
+// fewer than 2^15 items); bit 15 of each half tells that a published count is
+// there.  Published words go through relaxed agent-scope atomics: a word carries
+// its own value and no other data is published through it.
 #define SRT_AGG2 0x80008000u
 static_assert(HL_SORT_TILE_MAX < 0x8000, "a tile's digit count must fit 15 bits");
 __device__ __forceinline__ void srt_st_store(uint32_t* p, uint32_t w) {
@@ -48,10 +71,6 @@ __device__ __forceinline__ void srt_st_store(uint32_t* p, uint32_t w) {
 }
 __device__ __forceinline__ uint32_t srt_st_load(const uint32_t* p) {
   return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t srt_st_load2(const uint32_t* p) {  // two words (8-byte aligned)
-  return __hip_atomic_load(reinterpret_cast<uint64_t*>(const_cast<uint32_t*>(p)), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ uint32_t srt_n(const uint32_t* n_dev, uint32_t n_host) {
@@ -68,48 +87,96 @@ static srt_plan srt_make_plan(int bits) {
   srt_plan p;
   p.passes = (bits + 10) / 11;
   p.b = (bits + p.passes - 1) / p.passes;
-  p.nb = p.b <= 8 ? 256 : (p.b <= 10 ? 1024 : 2048);
+  p.nb = p.b <= 8 ? 256 : (p.b <= 9 ? 512 : (p.b <= 10 ? 1024 : 2048));
   return p;
 }
 
-// Per-block counts of every digit of every pass; clears n_zero status words.
-template <int NB>
-__global__ void __launch_bounds__(HL_SORT_HIST_THREADS)
-srt_hist(const uint32_t* __restrict__ keys, const uint32_t* n_dev, uint32_t n_host, int passes, int b,
-         uint32_t* __restrict__ part, uint32_t* __restrict__ zero, uint64_t n_zero) {
-  __shared__ uint32_t h[HL_SORT_MAXPASS][NB];
-  const uint32_t n = srt_n(n_dev, n_host);
-  const uint32_t gs = gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gs) zero[i] = 0;
-  for (int j = threadIdx.x; j < HL_SORT_MAXPASS * NB; j += blockDim.x) (&h[0][0])[j] = 0;
-  __syncthreads();
-  const uint32_t mask = (1u << b) - 1u;
-  for (uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += 8 * gs) {
-    uint32_t k[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) k[u] = i0 + u * gs < n ? keys[i0 + u * gs] : 0u;
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (i0 + u * gs < n)
-        for (int p = 0; p < passes; ++p) atomicAdd(&h[p][(k[u] >> (b * p)) & mask], 1u);
-  }
-  __syncthreads();
-  for (int p = 0; p < passes; ++p)
-    for (int j = threadIdx.x; j < NB; j += blockDim.x)
-      part[((size_t)p * HL_SORT_HIST_BLOCKS + blockIdx.x) * NB + j] = h[p][j];
+// the lookups that no bag covers, [0, first) and [covered, n), sort last
+__device__ __forceinline__ void srt_uncovered(const hl_sort_src& src, uint32_t n, uint32_t* first, uint32_t* covered) {
+  *first = (uint32_t)min((int64_t)max(src.bag_ptr[0], 0), (int64_t)n);
+  *covered = max((uint32_t)min((int64_t)max(src.bag_ptr[src.n_bags], 0), (int64_t)n), *first);
 }
 
-// Block-wide exclusive scans of two values per digit (each thread owns PER
-// consecutive digits).  Returns through a and c in place.
-template <int NB, int PER>
-__device__ __forceinline__ void srt_scan2(uint32_t (&a)[PER], uint32_t (&c)[PER], uint32_t (*ws)[2]) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  uint32_t sa = 0, sc = 0;
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    sa += a[j];
-    sc += c[j];
+// Digit counts of tile blockIdx.x for every pass (row[0], row[1], row[3]; the
+// words the first two passes publish, row[2], grp and gtot, are cleared).
+template <int NB>
+__global__ void __launch_bounds__(HL_SORT_THREADS)
+srt_count(hl_sort_src src, const uint32_t* n_dev, uint32_t n_host, int passes, int b, uint32_t tile,
+          uint32_t* __restrict__ row0, uint32_t* __restrict__ row1, uint32_t* __restrict__ row2,
+          uint32_t* __restrict__ row3, uint64_t* __restrict__ grp0, uint64_t* __restrict__ grp1,
+          uint64_t* __restrict__ gtot, uint32_t* err) {
+  __shared__ uint32_t h[HL_SORT_MAXPASS][NB];
+  bw_start_signal(src.sflag, src.sv);
+  const uint32_t n = srt_n(n_dev, n_host);
+  const uint32_t tb = blockIdx.x * tile, te = min(tb + tile, n);
+  const int tid = threadIdx.x;
+  for (int j = tid; j < HL_SORT_MAXPASS * NB; j += HL_SORT_THREADS) (&h[0][0])[j] = 0;
+  uint32_t first = 0, covered = n;
+  bool fits = false;
+  if (src.codes) {
+    srt_uncovered(src, n, &first, &covered);
+    fits = src.cf.table && *src.cf.ncold <= (uint32_t)src.cf.cap;
+    if (blockIdx.x == 0 && tid == 0) {
+      if (src.bag_ptr[src.n_bags] != (int64_t)n) hl_flag(err, HL_DEVERR_SHAPE);
+      if (src.cf.table && !fits) hl_flag(err, HL_DEVERR_CAPACITY);
+    }
   }
+  __syncthreads();
+  const uint32_t mask = (1u << b) - 1u;
+  bool bad = false;
+  for (uint32_t i0 = tb + tid; i0 < te; i0 += 4 * HL_SORT_THREADS) {
+    uint32_t k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t i = i0 + u * HL_SORT_THREADS;
+      k[u] = i < te ? (src.codes ? (uint32_t)src.codes[i] : src.k[i]) : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t i = i0 + u * HL_SORT_THREADS;
+      if (i >= te) continue;
+      uint32_t key = k[u];
+      if (src.codes) {
+        if (i < first || i >= covered) {
+          key = EB_SENT;
+        } else {
+          if (src.cf.table && key == 0xFFFFFFFFu) {
+            const uint32_t sl = src.cf.slotof[i];
+            key = (uint32_t)bw_fused_code(-1, i, src.cf, src.k_cap, fits);
+            if (key != 0xFFFFFFFFu) src.codes[i] = (int32_t)key;
+            if (sl < src.cf.S) src.cf.table[sl] = 0;
+          }
+          key = bw_key(key, src.n_hot, src.k_cap, src.stg_rows);
+          bad = bad || key == EB_SENT;
+        }
+      }
+      for (int p = 0; p < passes; ++p) atomicAdd(&h[p][(key >> (b * p)) & mask], 1u);
+    }
+  }
+  if (bad) hl_flag(err, HL_DEVERR_BAD_CODE);
+  __syncthreads();
+  constexpr int TW = NB / 2;
+  for (int j = tid; j < TW; j += HL_SORT_THREADS) {
+    const size_t o = (size_t)blockIdx.x * TW + j;
+    row0[o] = h[0][2 * j] | (h[0][2 * j + 1] << 16);
+    const bool lead = blockIdx.x % HL_SORT_GRP == 0;
+    const size_t go = (size_t)(blockIdx.x / HL_SORT_GRP) * TW + j;
+    if (lead) grp1[go] = 0;
+    if (blockIdx.x == 0) gtot[j] = 0;
+    if (passes > 1) {
+      row1[o] = h[1][2 * j] | (h[1][2 * j + 1] << 16);
+      row2[o] = 0;
+      if (lead) grp0[go] = 0;
+    }
+    if (passes > 2) row3[o] = h[2][2 * j] | (h[2][2 * j + 1] << 16);
+  }
+}
+
+// Block-wide exclusive scans of two values per digit, two consecutive digits
+// per thread, in place.
+__device__ __forceinline__ void srt_scan2(uint32_t (&a)[2], uint32_t (&c)[2], uint32_t (*ws)[2]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t sa = a[0] + a[1], sc = c[0] + c[1];
   uint32_t ia = sa, ic = sc;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -129,212 +196,428 @@ __device__ __forceinline__ void srt_scan2(uint32_t (&a)[PER], uint32_t (&c)[PER]
     ra += ws[j][0];
     rc += ws[j][1];
   }
+  a[1] = ra + a[0];
+  a[0] = ra;
+  c[1] = rc + c[0];
+  c[0] = rc;
+}
+
+// Sums over the tiles' counts of one pass, 64 words (128 digits) per block, 16
+// groups of tiles at a time (a wave each).  The digits' totals: of the first
+// pass (p = 0) published as flagged 64-bit words with every group's prefix over
+// the groups before it, since tile blocks of the same launch wait for them; of a
+// later pass stored for its launch.
+template <int NB>
+__device__ __forceinline__ void srt_sums(uint32_t blk, uint32_t tiles, const uint32_t* __restrict__ row0,
+                                         const uint32_t* __restrict__ row1, const uint32_t* __restrict__ row3,
+                                         uint64_t* gpre, uint64_t* gtot, uint32_t* __restrict__ tot,
+                                         uint32_t (*sum)[128]) {
+  constexpr int TW = NB / 2, PB = TW / 64;  // blocks per pass
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int p = (int)(blk / PB);
+  const uint32_t w0 = (blk % PB) * 64, j = w0 + lane;
+  const uint32_t* row = p == 0 ? row0 : (p == 1 ? row1 : row3);
+  const uint32_t groups = (tiles + HL_SORT_GRP - 1) / HL_SORT_GRP;
+  uint32_t a = 0, c = 0;  // (threads 0..63: the two digits of word j over the groups so far)
+  for (uint32_t g0 = 0; g0 < groups; g0 += HL_SORT_WAVES) {
+    uint32_t x[HL_SORT_GRP], sa = 0, sc = 0;
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const uint32_t ta = a[j], tc = c[j];
-    a[j] = ra;
-    c[j] = rc;
-    ra += ta;
-    rc += tc;
+    for (int u = 0; u < HL_SORT_GRP; ++u) {
+      const uint32_t t = (g0 + w) * HL_SORT_GRP + u;
+      x[u] = t < tiles ? (row + (size_t)t * TW)[j] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < HL_SORT_GRP; ++u) {
+      sa += x[u] & 0xFFFFu;
+      sc += x[u] >> 16;
+    }
+    sum[w][2 * lane] = sa;
+    sum[w][2 * lane + 1] = sc;
+    __syncthreads();
+    if (w == 0)
+      for (uint32_t q = 0; q < HL_SORT_WAVES && g0 + q < groups; ++q) {
+        if (p == 0) hl_st_store(gpre + (size_t)(g0 + q) * TW + j, SRT_GRP2 | (uint64_t)c << 32 | a);
+        a += sum[q][2 * lane];
+        c += sum[q][2 * lane + 1];
+      }
+    __syncthreads();
+  }
+  if (w != 0) return;
+  if (p == 0) {
+    hl_st_store(gtot + j, SRT_GRP2 | (uint64_t)c << 32 | a);
+  } else {
+    tot[(size_t)p * HL_SORT_MAXNB + 2 * j] = a;
+    tot[(size_t)p * HL_SORT_MAXNB + 2 * j + 1] = c;
   }
 }
 
-template <int NB, int ITEMS>
+// A flagged 64-bit word, waited for.
+__device__ __forceinline__ uint64_t srt_wait(const uint64_t* p, uint32_t* err) {
+  uint32_t spins = 0;
+  for (;;) {
+    const uint64_t x = hl_st_load(p);
+    if ((x & SRT_GRP2) == SRT_GRP2) return x & ~SRT_GRP2;
+    if (++spins > HL_SPIN_LIMIT) {
+      hl_flag(err, HL_DEVERR_STALL);
+      return 0;
+    }
+  }
+}
+
+// The bag of each lookup [tb, te) into bag[i - tb] (lookups no bag covers keep
+// what is there).  Thread i holds the bounds p, q of bag g0 + i, a window of bags
+// around where the first lookup would be if all bags were alike: when it holds
+// all of the tile's bags each thread writes its own, else the bag of the first
+// lookup is found in it or searched by the whole block, HL_SORT_THREADS probes of
+// bag_ptr a round, and each bag from there on writes its lookups.
+__device__ __forceinline__ void srt_bag(uint32_t j, int64_t p, int64_t q, uint32_t tb, uint32_t te, uint32_t* bag) {
+  const uint32_t lo = (uint32_t)max(p, (int64_t)tb), hi = (uint32_t)min(max(q, (int64_t)0), (int64_t)te);
+  for (uint32_t i = lo; i < hi; ++i) bag[i - tb] = j;
+}
+// (c: the window's bags that start at or before lookup tb, a prefix of it;
+// reach: the window's last bag ends at or after te)
+__device__ __forceinline__ void srt_bags(const hl_sort_src& src, bool window, int64_t g0, int32_t p, int32_t q, int c,
+                                         bool reach, uint32_t tb, uint32_t te, uint32_t* bag) {
+  const int64_t mine = g0 + threadIdx.x;
+  const bool ends = g0 + HL_SORT_THREADS >= src.n_bags;
+  const bool starts = window && (c > 0 || g0 == 0);
+  if (starts && (ends || reach)) {
+    if (mine < src.n_bags) srt_bag((uint32_t)mine, p, q, tb, te, bag);
+    return;
+  }
+  int64_t a = g0 + (c > 0 ? c - 1 : 0);
+  if (!starts || (c == HL_SORT_THREADS && !ends)) {
+    int64_t e = src.n_bags;
+    for (a = 0; e - a > 1;) {
+      const int64_t step = (e - a + HL_SORT_THREADS - 1) / HL_SORT_THREADS;
+      const int64_t j = a + threadIdx.x * step;
+      const int k = __syncthreads_count(j < e && src.bag_ptr[j] <= (int32_t)tb);
+      a += (k > 0 ? k - 1 : 0) * step;
+      e = min(a + step, e);
+    }
+  }
+  for (int64_t j = a + threadIdx.x; j < src.n_bags; j += HL_SORT_THREADS) {
+    const int32_t jp = src.bag_ptr[j], jq = src.bag_ptr[j + 1];
+    if (jp >= (int32_t)te) break;
+    srt_bag((uint32_t)j, jp, jq, tb, te, bag);
+  }
+}
+
+template <int NB, int ITEMS, bool FIRST>
 __global__ void __launch_bounds__(HL_SORT_THREADS)
-srt_pass(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
-         uint32_t* __restrict__ vout, const uint32_t* n_dev, uint32_t n_host, int shift, int b,
-         const uint32_t* __restrict__ part, uint32_t n_part, uint32_t* st, uint32_t* st_next, uint32_t* tile_ctr,
+srt_pass(hl_sort_src src, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+         uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, const uint32_t* n_dev, uint32_t n_host,
+         uint32_t tiles, uint32_t sums, int shift, int b, const uint32_t* __restrict__ row1,
+         const uint32_t* __restrict__ row3, uint64_t* gtot, uint32_t* __restrict__ tot, uint32_t* st, uint64_t* grp, uint32_t* st_next, uint64_t* grp_next, uint32_t* tile_ctr,
          uint32_t* err, hl_hook hk) {
   constexpr uint32_t TILE = HL_SORT_THREADS * ITEMS;
-  constexpr int PER = NB >= HL_SORT_THREADS ? NB / HL_SORT_THREADS : 1;
-  constexpr int OWNERS = NB / PER;         // threads that own digits
-  // status words of a tile per digit owner, and the earlier tiles whose
-  // counts one round reads (48 words in flight per thread)
-  constexpr int PW = PER >= 2 ? PER / 2 : 1;
-  constexpr int CHUNK = 48 / PW;
-  constexpr size_t TW = PER >= 2 ? NB / 2 : NB;  // words per tile
+  constexpr uint32_t TW = NB / 2;                // words of two digits
+  constexpr uint32_t SP = HL_SORT_THREADS / TW;  // threads per word: each reads every SP-th tile's count
   __shared__ uint32_t s_tile;
-  __shared__ uint32_t wcnt[HL_SORT_WAVES][NB];
+  __shared__ uint32_t wcnt[HL_SORT_WAVES][TW];   // per wave, two digits a word (a wave has at most 512 items)
   __shared__ uint32_t tdex[NB], gbase[NB];
   __shared__ uint32_t scan_ws[HL_SORT_WAVES][2];
   __shared__ uint32_t lk[TILE], lv[TILE];
+  __shared__ uint32_t part[SP > 1 ? 4 : 1][SP > 1 ? HL_SORT_THREADS : 1];
   const uint32_t n = srt_n(n_dev, n_host);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   hl_hook_head(hk);
-  if (tid == 0) s_tile = atomicInc(tile_ctr, gridDim.x - 1);
-  for (int j = tid; j < HL_SORT_WAVES * NB; j += HL_SORT_THREADS) (&wcnt[0][0])[j] = 0;
+  if (tid == 0) s_tile = atomicInc(tile_ctr, tiles + sums - 1);
   __syncthreads();
-  const uint32_t tile = s_tile;
-  if (st_next)  // this tile's status words of the next pass
-    for (int j = tid; j < (int)TW; j += HL_SORT_THREADS) st_next[(size_t)tile * TW + j] = 0;
+  if (FIRST && s_tile < sums) {
+    static_assert(HL_SORT_WAVES * 128 <= TW * HL_SORT_WAVES, "the sums' LDS");
+    srt_sums<NB>(s_tile, tiles, st, row1, row3, grp, gtot, tot, reinterpret_cast<uint32_t(*)[128]>(&wcnt[0][0]));
+    return;
+  }
+  const uint32_t tile = s_tile - sums;
+  if (!FIRST && st_next)  // this tile's published words of the next pass
+    for (uint32_t j = tid; j < TW; j += HL_SORT_THREADS) {
+      st_next[(size_t)tile * TW + j] = 0;
+      if (tile % HL_SORT_GRP == 0) grp_next[(size_t)(tile / HL_SORT_GRP) * TW + j] = 0;
+    }
   const uint64_t tb = (uint64_t)tile * TILE;
   if (tb >= n) return;
+  const uint32_t te = (uint32_t)min(tb + TILE, (uint64_t)n);
   const uint32_t mask = (1u << b) - 1u;
+  const uint32_t i0 = (uint32_t)tb + w * (ITEMS * 64) + lane;  // item k: i0 + 64 k
   uint32_t key[ITEMS], val[ITEMS];
+  const bool from_codes = FIRST && src.codes;
+  bool one = from_codes && src.n_bags == (int64_t)n;  // every bag of the tile holds its own lookup alone?
+  int32_t lo[ITEMS], hi[ITEMS], gp = 0, gq = 0;
+  int64_t g0 = 0;
+  uint32_t first = 0, covered = n;
+  if (from_codes) srt_uncovered(src, n, &first, &covered);
+  if (from_codes && !one) {
+    g0 = max((int64_t)(tb * (uint64_t)src.n_bags / n) - HL_SORT_THREADS / 4, (int64_t)0);
+    const int64_t j = min(g0 + tid, src.n_bags - 1);
+    gp = src.bag_ptr[j];
+    gq = src.bag_ptr[j + 1];
+  }
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const uint64_t idx = tb + (uint64_t)w * (ITEMS * 64) + k * 64 + lane;
-    const bool ok = idx < n;
-    key[k] = ok ? kin[idx] : 0xFFFFFFFFu;
-    val[k] = ok ? vin[idx] : 0u;
-  }
-  // global counts of the owned digits: loads issued with the keys', summed
-  // after the ranking (which waits only for the keys)
-  const int d0 = tid * PER;
-  const bool owner = tid < OWNERS;
-  uint32_t pv[PER][HL_SORT_HIST_BLOCKS];
-#pragma unroll
-  for (int q = 0; q < HL_SORT_HIST_BLOCKS; ++q) {
-    const bool in = owner && (uint32_t)q < n_part;
-    if constexpr (PER >= 2) {  // two digits per load
-#pragma unroll
-      for (int j = 0; j < PER; j += 2) {
-        const uint2 x = in ? *reinterpret_cast<const uint2*>(part + (size_t)q * NB + d0 + j) : make_uint2(0u, 0u);
-        pv[j][q] = x.x;
-        pv[j + 1][q] = x.y;
+    const uint32_t i = min(i0 + 64 * k, te - 1);
+    if (from_codes) {
+      key[k] = (uint32_t)src.codes[i];
+      if (one) {
+        lo[k] = src.bag_ptr[i];
+        hi[k] = src.bag_ptr[i + 1];
       }
     } else {
-      pv[0][q] = in ? part[(size_t)q * NB + d0] : 0u;
+      key[k] = kin[i];
+      val[k] = vin[i];
     }
+  }
+  for (uint32_t j = tid; j < HL_SORT_WAVES * TW; j += HL_SORT_THREADS) (&wcnt[0][0])[j] = 0;
+  const uint32_t wd = (uint32_t)tid % TW;
+  const uint32_t sp = __builtin_amdgcn_readfirstlane((uint32_t)tid / TW);  // (a wave's words share it)
+  // word wd's digits in the earlier tiles of this tile's group of HL_SORT_GRP:
+  // the first pass has them from srt_count
+  const uint32_t grp0 = tile / HL_SORT_GRP, in_grp = tile % HL_SORT_GRP;
+  constexpr int GT = (HL_SORT_GRP - 1 + SP - 1) / SP;
+  uint32_t excl[2] = {0, 0};
+  uint2 dt = make_uint2(0u, 0u);  // the digits' totals over all tiles
+  if (FIRST) {
+    uint32_t wv[GT];
+#pragma unroll
+    for (int q = 0; q < GT; ++q) {
+      const uint32_t t = sp + q * SP;
+      wv[q] = t < in_grp ? (st + (size_t)(grp0 * HL_SORT_GRP + t) * TW)[wd] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < GT; ++q) {
+      excl[0] += wv[q] & 0xFFFFu;
+      excl[1] += wv[q] >> 16;
+    }
+    if constexpr (SP > 1) {
+      part[2][tid] = excl[0];
+      part[3][tid] = excl[1];
+    }
+  } else if (sp == 0) {
+    dt = *reinterpret_cast<const uint2*>(tot + 2 * wd);
+  }
+  if (from_codes) {
+    if (one)
+#pragma unroll
+      for (int k = 0; k < ITEMS; ++k) {
+        const int32_t i = (int32_t)min(i0 + 64 * k, te - 1);
+        one = one && lo[k] == i && hi[k] == i + 1;
+      }
+    // one barrier for what the block has to agree on: whether every bag of the
+    // tile is its own lookup's; else how many of the window's bags start by
+    // lookup tb, and whether the window reaches te
+    const bool window = src.n_bags != (int64_t)n;
+    const uint64_t in = __ballot(g0 + tid < src.n_bags && gp <= (int32_t)tb);
+    const uint64_t bad = __ballot(!one);
+    if (lane == 63) {
+      scan_ws[w][0] = (uint32_t)__popcll(in);
+      scan_ws[w][1] = (bad ? 1u : 0u) | (w == HL_SORT_WAVES - 1 && gq >= (int32_t)te ? 2u : 0u);
+    }
+    __syncthreads();  // (wcnt is zero now, too)
+    uint32_t c = 0, fl = 0;
+#pragma unroll
+    for (int q = 0; q < HL_SORT_WAVES; ++q) {
+      c += scan_ws[q][0];
+      fl |= scan_ws[q][1];
+    }
+    if (fl & 1u) {
+      srt_bags(src, window, g0, gp, gq, (int)c, (fl & 2u) != 0, (uint32_t)tb, te, lk);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < ITEMS; ++k) val[k] = lk[w * (ITEMS * 64) + 64 * k + lane];
+      // (lk takes the reordered tile after the barriers below)
+    } else {
+#pragma unroll
+      for (int k = 0; k < ITEMS; ++k) val[k] = i0 + 64 * k;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t i = i0 + 64 * k;
+      key[k] = i >= first && i < covered ? bw_key(key[k], src.n_hot, src.k_cap, src.stg_rows) : EB_SENT;
+    }
+  } else {
+    __syncthreads();  // wcnt is zero
   }
   // ranking, stable by construction: for each item slot the lanes holding the
   // same digit find one another with one ballot per digit bit (their peer
   // mask); the lowest peer adds the group's size to the wave's counter of that
   // digit (one atomic per distinct digit, so no two lanes of an instruction
-  // touch one counter) and the others take its old value by a lane shuffle;
-  // a lane's rank is that value plus its peers on lower lanes.  A wave's LDS
-  // instructions execute in issue order, so the counters advance in item
-  // order: ranks follow (item, lane) order, which is index order.
-  uint32_t dg[ITEMS], lr[ITEMS];
-  const uint64_t lt = (1ull << lane) - 1ull;
+  // touch one digit's count) and the others take its old value by a lane
+  // shuffle; a lane's rank is that value plus its peers on lower lanes.  A
+  // wave's LDS instructions execute in issue order, so the counters advance in
+  // item order: ranks follow (item, lane) order, which is index order.  The
+  // peer masks, the atomics and the shuffles of all items are issued as three
+  // groups, so that an item's latency hides behind the others'.
+  uint32_t lr[ITEMS];
+  {
+    uint64_t peers[ITEMS];
+    uint32_t old[ITEMS];
 #pragma unroll
-  for (int k = 0; k < ITEMS; ++k) {
-    const uint64_t idx = tb + (uint64_t)w * (ITEMS * 64) + k * 64 + lane;
-    const bool valid = idx < n;
-    dg[k] = (key[k] >> shift) & mask;
-    const uint64_t peers = hl_match_digit(dg[k], b, valid);
-    const int leader = __ffsll((unsigned long long)peers) - 1;
-    uint32_t base = 0;
-    if (valid && lane == leader) base = atomicAdd(&wcnt[w][dg[k]], (uint32_t)__popcll(peers));
-    base = __shfl(base, leader < 0 ? 0 : leader);
-    lr[k] = valid ? base + (uint32_t)__popcll(peers & lt) : 0u;
-  }
-  uint32_t dtot[PER];
+    for (int k = 0; k < ITEMS; ++k)
+      peers[k] = hl_match_digit((key[k] >> shift) & mask, b, i0 + 64 * k < te);
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    dtot[j] = 0;
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t d = (key[k] >> shift) & mask;
+      old[k] = 0;
+      if (peers[k] && lane == __ffsll((unsigned long long)peers[k]) - 1)
+        old[k] = atomicAdd(&wcnt[w][d >> 1], (uint32_t)__popcll(peers[k]) << (16 * (d & 1)));
+    }
+    const uint64_t lt = (1ull << lane) - 1ull;
 #pragma unroll
-    for (int q = 0; q < HL_SORT_HIST_BLOCKS; ++q) dtot[j] += pv[j][q];
-  }
-  __syncthreads();
-  // wave-exclusive offsets of each owned digit; the totals are the tile's
-  // counts, published at once for the later tiles
-  uint32_t tc[PER], tx[PER];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    uint32_t run = 0;
-    if (owner)
-#pragma unroll
-      for (int q = 0; q < HL_SORT_WAVES; ++q) {
-        const uint32_t c = wcnt[q][d0 + j];
-        wcnt[q][d0 + j] = run;
-        run += c;
-      }
-    tc[j] = run;
-    tx[j] = run;
-  }
-  if (owner) {
-    if constexpr (PER >= 2) {
-#pragma unroll
-      for (int j = 0; j < PER; j += 2)
-        srt_st_store(st + (size_t)tile * TW + (d0 + j) / 2, SRT_AGG2 | tc[j] | (tc[j + 1] << 16));
-    } else {
-      srt_st_store(st + (size_t)tile * TW + d0, SRT_AGG | tc[0]);
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t d = (key[k] >> shift) & mask;
+      const int leader = __ffsll((unsigned long long)peers[k]) - 1;
+      const uint32_t x = __shfl(old[k], leader < 0 ? 0 : leader);
+      lr[k] = ((x >> (16 * (d & 1))) & 0xFFFFu) + (uint32_t)__popcll(peers[k] & lt);
     }
   }
-  uint32_t gx[PER];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) gx[j] = dtot[j];
-  srt_scan2<NB, PER>(tx, gx, scan_ws);
-  if (owner)
-#pragma unroll
-    for (int j = 0; j < PER; ++j) tdex[d0 + j] = tx[j];
   __syncthreads();
-  // the tile in digit order in LDS (its own offsets are known now; the
-  // earlier tiles' counts are read below)
+  // wave-exclusive offsets of word wd's digits (both at once: a tile has fewer
+  // than 2^15 items); the totals are the tile's counts, which a later pass
+  // publishes at once for the later tiles
+  uint32_t tx[2] = {0, 0}, gx[2] = {0, 0}, mine[2] = {0, 0};
+  if (sp == 0) {
+    uint32_t run = 0;
+#pragma unroll
+    for (int q = 0; q < HL_SORT_WAVES; ++q) {
+      const uint32_t c = wcnt[q][wd];
+      wcnt[q][wd] = run;
+      run += c;
+    }
+    if (!FIRST) srt_st_store(st + (size_t)tile * TW + wd, SRT_AGG2 | run);
+    tx[0] = mine[0] = run & 0xFFFFu;
+    tx[1] = mine[1] = run >> 16;
+    if constexpr (FIRST) {
+      if constexpr (SP > 1)
+        for (uint32_t q = 1; q < SP; ++q) {
+          excl[0] += part[2][tid + q * TW];
+          excl[1] += part[3][tid + q * TW];
+        }
+      // from the launch's first blocks, which wait for nothing
+      const uint64_t gt = srt_wait(gtot + wd, err), gp0 = srt_wait(grp + (size_t)grp0 * TW + wd, err);
+      dt = make_uint2((uint32_t)gt, (uint32_t)(gt >> 32));
+      excl[0] += (uint32_t)gp0;
+      excl[1] += (uint32_t)(gp0 >> 32);
+    }
+    gx[0] = dt.x;
+    gx[1] = dt.y;
+  }
+  srt_scan2(tx, gx, scan_ws);
+  if (sp == 0)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      tdex[2 * wd + j] = tx[j];
+      if (FIRST) gbase[2 * wd + j] = gx[j] + excl[j] - tx[j];
+    }
+  __syncthreads();
+  // the tile in digit order in LDS (its own offsets are known now; a later
+  // pass reads the earlier tiles' counts below)
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const uint64_t idx = tb + (uint64_t)w * (ITEMS * 64) + k * 64 + lane;
-    if (idx < n) {
-      const uint32_t p = tdex[dg[k]] + wcnt[w][dg[k]] + lr[k];
+    if (i0 + 64 * k < te) {
+      const uint32_t d = (key[k] >> shift) & mask;
+      const uint32_t p = tdex[d] + ((wcnt[w][d >> 1] >> (16 * (d & 1))) & 0xFFFFu) + lr[k];
       lk[p] = key[k];
       lv[p] = val[k];
     }
   }
-  // counts of each owned digit in all earlier tiles: their published counts,
-  // read CHUNK tiles at a time with every load in flight (no chain through
-  // inclusive prefixes); a round with an unpublished word is read again
-  uint32_t excl[PER];
+  if (!FIRST) {
+    // counts of word wd's digits in all earlier tiles, in two steps of loads that
+    // are all in flight together (no chain through inclusive prefixes): the
+    // earlier tiles of this tile's group of HL_SORT_GRP, then the earlier groups,
+    // whose counts their last tiles publish; a step with an unpublished word is
+    // read again
+    constexpr int GC = 16;
+    uint32_t spins = 0;
+    for (bool again = in_grp > sp; again;) {
+      uint32_t wv[GT], ready = SRT_AGG2, s0 = 0, s1 = 0;
 #pragma unroll
-  for (int j = 0; j < PER; ++j) excl[j] = 0;
-  uint32_t spins = 0;
-  for (uint32_t q0 = 0; owner && q0 < tile; q0 += CHUNK) {
-    for (;;) {
-      uint32_t wv[CHUNK][PW];
-#pragma unroll
-      for (int q = 0; q < CHUNK; ++q) {
-        const bool in = q0 + q < tile;
-        const uint32_t* a = st + (size_t)(q0 + q) * TW + (PER >= 2 ? d0 / 2 : d0);
-        if constexpr (PW == 2) {
-          const uint64_t x = in ? srt_st_load2(a) : ((uint64_t)SRT_AGG2 << 32 | SRT_AGG2);
-          wv[q][0] = (uint32_t)x;
-          wv[q][1] = (uint32_t)(x >> 32);
-        } else {
-          wv[q][0] = in ? srt_st_load(a) : (PER >= 2 ? SRT_AGG2 : SRT_AGG);
-        }
+      for (int q = 0; q < GT; ++q) {
+        const uint32_t t = sp + q * SP;
+        wv[q] = t < in_grp ? srt_st_load(st + (size_t)(grp0 * HL_SORT_GRP + t) * TW + wd) : SRT_AGG2;
       }
-      bool ready = true;
-      uint32_t sum[PER];
 #pragma unroll
-      for (int j = 0; j < PER; ++j) sum[j] = 0;
-#pragma unroll
-      for (int q = 0; q < CHUNK; ++q)
-#pragma unroll
-        for (int x = 0; x < PW; ++x) {
-          const uint32_t v = wv[q][x];
-          if constexpr (PER >= 2) {
-            ready = ready && (v & SRT_AGG2) == SRT_AGG2;
-            sum[2 * x] += v & 0x7FFFu;
-            sum[2 * x + 1] += (v >> 16) & 0x7FFFu;
-          } else {
-            ready = ready && (v & SRT_AGG) != 0;
-            sum[0] += v & SRT_VAL;
-          }
-        }
-      if (ready) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) excl[j] += sum[j];
-        break;
+      for (int q = 0; q < GT; ++q) {
+        ready &= wv[q];
+        s0 += wv[q] & 0x7FFFu;
+        s1 += (wv[q] >> 16) & 0x7FFFu;
       }
-      if (++spins > HL_SPIN_LIMIT) {
+      again = ready != SRT_AGG2;
+      if (!again) {
+        excl[0] = s0;
+        excl[1] = s1;
+      } else if (++spins > HL_SPIN_LIMIT) {
         hl_flag(err, HL_DEVERR_STALL);
-        break;
+        again = false;
       }
-      __builtin_amdgcn_s_sleep(1);
     }
-  }
-  if (owner)
+    if constexpr (SP > 1) {
+      part[2][tid] = excl[0];
+      part[3][tid] = excl[1];
+      __syncthreads();
+      if (sp == 0)
+        for (uint32_t q = 1; q < SP; ++q) {
+          excl[0] += part[2][tid + q * TW];
+          excl[1] += part[3][tid + q * TW];
+        }
+      else
+        excl[0] = excl[1] = 0;
+    }
+    if (in_grp == HL_SORT_GRP - 1 && sp == 0)
+      hl_st_store(grp + (size_t)grp0 * TW + wd,
+                  SRT_GRP2 | (uint64_t)(excl[1] + mine[1]) << 32 | (excl[0] + mine[0]));
+    for (uint32_t q0 = sp; q0 < grp0; q0 += SP * GC) {
+      for (;;) {
+        uint64_t wv[GC], ready = SRT_GRP2;
+        uint32_t s0 = 0, s1 = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) gbase[d0 + j] = gx[j] + excl[j];
+        for (int q = 0; q < GC; ++q) {
+          const uint32_t t = q0 + q * SP;
+          wv[q] = t < grp0 ? hl_st_load(grp + (size_t)t * TW + wd) : SRT_GRP2;
+        }
+#pragma unroll
+        for (int q = 0; q < GC; ++q) {
+          ready &= wv[q];
+          s0 += (uint32_t)wv[q] & 0x7FFFFFFFu;
+          s1 += (uint32_t)(wv[q] >> 32) & 0x7FFFFFFFu;
+        }
+        if ((ready & SRT_GRP2) == SRT_GRP2) {
+          excl[0] += s0;
+          excl[1] += s1;
+          break;
+        }
+        if (++spins > HL_SPIN_LIMIT) {
+          hl_flag(err, HL_DEVERR_STALL);
+          break;
+        }
+      }
+    }
+    if constexpr (SP > 1) {
+      part[0][tid] = excl[0];
+      part[1][tid] = excl[1];
+      __syncthreads();
+      if (sp == 0)
+        for (uint32_t q = 1; q < SP; ++q) {
+          excl[0] += part[0][tid + q * TW];
+          excl[1] += part[1][tid + q * TW];
+        }
+    }
+    if (sp == 0)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) gbase[2 * wd + j] = gx[j] + excl[j] - tx[j];
+  }
   __syncthreads();
-  const uint32_t nv = (uint32_t)min((uint64_t)TILE, (uint64_t)n - tb);
-#pragma unroll 4
-  for (uint32_t i = tid; i < nv; i += HL_SORT_THREADS) {
+  // (gbase: an item's place less its place in the tile)
+  const uint32_t nv = te - (uint32_t)tb;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t i = tid + k * HL_SORT_THREADS;
+    if (i >= nv) break;
     const uint32_t kk = lk[i];
-    const uint32_t d = (kk >> shift) & mask;
-    const uint32_t p = gbase[d] + (i - tdex[d]);
-    kout[p] = kk;
-    vout[p] = lv[i];
+    const uint32_t p = gbase[(kk >> shift) & mask] + i;
+    if (p < n) {  // (always, for counts of the same keys)
+      kout[p] = kk;
+      vout[p] = lv[i];
+    }
   }
 }
 
@@ -352,78 +635,60 @@ int hl_stream_cus(hipStream_t s) {
   return c;
 }
 
-hl_sort_geom hl_sort_geometry(uint32_t n_host, int bits, int cus) {
-  const srt_plan pl = srt_make_plan(bits);
-  hl_sort_geom g;
-  g.passes = pl.passes;
-  g.b = pl.b;
-  g.nb = pl.nb;
-  const uint32_t hb = hl_div_up(n_host, HL_SORT_HIST_THREADS * 8);
-  g.hist_blocks = hb < 1 ? 1 : (hb > HL_SORT_HIST_BLOCKS ? HL_SORT_HIST_BLOCKS : hb);
+// items per thread of a tile: the fewest that keep a sort to HL_SORT_TILES_AIM
+// tiles and to the stream's compute units (one tile per unit, one round)
+static int srt_items(uint32_t n_host, int cus) {
   const uint32_t aim = cus > 0 && cus < HL_SORT_TILES_AIM ? (uint32_t)cus : HL_SORT_TILES_AIM;
-  g.items = 12;
-  for (int it : {4, 6})
-    if (hl_div_up(n_host, HL_SORT_THREADS * it) <= aim) {
-      g.items = it;
-      break;
-    }
-  g.tile = HL_SORT_THREADS * g.items;
-  g.n_zero = (uint64_t)hl_div_up(n_host, g.tile) * pl.nb;
-  return g;
-}
-
-template <int NB>
-static hl_status srt_hist_launch(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uint32_t n_host, int bits,
-                                 hipStream_t s) {
-  const hl_sort_geom g = hl_sort_geometry(n_host, bits, hl_stream_cus(s));
-  HL_KERNEL(h, s, "srt_hist", srt_hist<NB>, dim3(g.hist_blocks), dim3(HL_SORT_HIST_THREADS), 0, s, ws.k0, n_dev,
-            n_host, g.passes, g.b, ws.part, ws.st[0], g.n_zero);
-  HL_LAUNCHED();
-  return HL_OK;
+  for (int it : {1, 2, 4})
+    if (hl_div_up(n_host, HL_SORT_THREADS * it) <= aim) return it;
+  return 8;
 }
 
 template <int NB, int ITEMS>
-static hl_status srt_launch(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uint32_t n_host, int bits,
-                            hipStream_t s) {
-  const hl_sort_geom g = hl_sort_geometry(n_host, bits, hl_stream_cus(s));
-  const uint32_t tiles = hl_div_up(n_host, g.tile);
+static hl_status srt_launch(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, const uint32_t* n_dev,
+                            uint32_t n_host, int bits, hipStream_t s) {
+  const srt_plan pl = srt_make_plan(bits);
+  const uint32_t tiles = hl_div_up(n_host, HL_SORT_THREADS * ITEMS);
+  const hl_hook hk = hl_hook_take(h);  // (carried by the first pass: srt_count's writes are complete then)
+  HL_KERNEL(h, s, "srt_count", srt_count<NB>, dim3(tiles), dim3(HL_SORT_THREADS), 0, s, src, n_dev, n_host, pl.passes,
+            pl.b, (uint32_t)(HL_SORT_THREADS * ITEMS), ws.row[0], ws.row[1], ws.row[2], ws.row[3], ws.grp[0],
+            ws.grp[1], ws.gtot, h->d_err);
   uint32_t *ki = ws.k0, *vi = ws.v0, *ko = ws.k1, *vo = ws.v1;
-  for (int p = 0; p < g.passes; ++p) {
-    HL_KERNEL(h, s, "srt_pass", (srt_pass<NB, ITEMS>), dim3(tiles), dim3(HL_SORT_THREADS), 0, s, ki, vi, ko, vo, n_dev,
-              n_host, g.b * p, g.b, ws.part + (size_t)p * HL_SORT_HIST_BLOCKS * NB, g.hist_blocks, ws.st[p & 1],
-              p + 1 < g.passes ? ws.st[(p + 1) & 1] : nullptr, ws.ctr + 1 + p, h->d_err,
-              p == 0 ? hl_hook_take(h) : hl_hook{});
-    uint32_t* t = ki;
-    ki = ko;
-    ko = t;
-    t = vi;
-    vi = vo;
-    vo = t;
+  // the published counts of the second pass go to row[2], of the third to row[0]
+  // (the first pass's counts, done with by then; cleared by the second pass)
+  const uint32_t sums = (uint32_t)pl.passes * (NB / 128);
+  HL_KERNEL(h, s, "srt_pass", (srt_pass<NB, ITEMS, true>), dim3(tiles + sums), dim3(HL_SORT_THREADS), 0, s, src, ki, vi,
+            ko, vo, n_dev, n_host, tiles, sums, 0, pl.b, ws.row[1], ws.row[3], ws.gtot, ws.tot, ws.row[0], ws.grp[1],
+            nullptr, nullptr, ws.ctr, h->d_err, hk);
+  for (int p = 1; p < pl.passes; ++p) {
+    std::swap(ki, ko);
+    std::swap(vi, vo);
+    HL_KERNEL(h, s, "srt_pass", (srt_pass<NB, ITEMS, false>), dim3(tiles), dim3(HL_SORT_THREADS), 0, s, src, ki, vi, ko,
+              vo, n_dev, n_host, tiles, 0u, pl.b * p, pl.b, nullptr, nullptr, nullptr,
+              ws.tot + (size_t)p * HL_SORT_MAXNB, ws.row[p == 1 ? 2 : 0], ws.grp[p - 1],
+              p == 1 && pl.passes > 2 ? ws.row[0] : nullptr, ws.grp[1], ws.ctr + p, h->d_err, hl_hook{});
   }
   HL_LAUNCHED();
   return HL_OK;
 }
 
-static hl_status srt_check(const hl_sort_ws& ws, uint32_t n_host, int bits) {
-  if (n_host > ws.n_max || n_host >= (1u << 30)) return HL_ERR_CAPACITY;
-  if (bits > 32) return HL_ERR_UNSUPPORTED;
-  return HL_OK;
-}
-
-hl_status hl_sort_passes(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uint32_t n_host, int bits,
-                         hipStream_t s, uint32_t** out_k, uint32_t** out_v) {
+static hl_status srt_run(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, const uint32_t* n_dev, uint32_t n_host,
+                         int bits, hipStream_t s, uint32_t** out_k, uint32_t** out_v) {
   *out_k = ws.k0;
   *out_v = ws.v0;
   if (n_host == 0) return HL_OK;
-  hl_status st = srt_check(ws, n_host, bits);
-  if (st != HL_OK) return st;
-  const hl_sort_geom g = hl_sort_geometry(n_host, bits, hl_stream_cus(s));
-#define SRT(NB)                                                                       \
-  (g.items == 4 ? srt_launch<NB, 4>(h, ws, n_dev, n_host, bits, s)                    \
-                : g.items == 6 ? srt_launch<NB, 6>(h, ws, n_dev, n_host, bits, s)     \
-                               : srt_launch<NB, 12>(h, ws, n_dev, n_host, bits, s))
-  if (g.nb == 256) st = SRT(256);
-  else if (g.nb == 1024) st = SRT(1024);
+  if (n_host > ws.n_max || n_host >= (1u << 30)) return HL_ERR_CAPACITY;
+  if (bits > 32) return HL_ERR_UNSUPPORTED;
+  const int items = srt_items(n_host, hl_stream_cus(s)), nb = srt_make_plan(bits).nb;
+  hl_status st;
+#define SRT(NB)                                                                        \
+  (items == 1   ? srt_launch<NB, 1>(h, ws, src, n_dev, n_host, bits, s)               \
+   : items == 2 ? srt_launch<NB, 2>(h, ws, src, n_dev, n_host, bits, s)               \
+   : items == 4 ? srt_launch<NB, 4>(h, ws, src, n_dev, n_host, bits, s)               \
+                : srt_launch<NB, 8>(h, ws, src, n_dev, n_host, bits, s))
+  if (nb == 256) st = SRT(256);
+  else if (nb == 512) st = SRT(512);
+  else if (nb == 1024) st = SRT(1024);
   else st = SRT(2048);
 #undef SRT
   if (st != HL_OK) return st;
@@ -433,15 +698,12 @@ hl_status hl_sort_passes(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, ui
 
 hl_status hl_sort_pairs(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uint32_t n_host, int bits,
                         hipStream_t s, uint32_t** out_k, uint32_t** out_v) {
-  *out_k = ws.k0;
-  *out_v = ws.v0;
-  if (n_host == 0) return HL_OK;
-  hl_status st = srt_check(ws, n_host, bits);
-  if (st != HL_OK) return st;
-  const srt_plan pl = srt_make_plan(bits);
-  if (pl.nb == 256) st = srt_hist_launch<256>(h, ws, n_dev, n_host, bits, s);
-  else if (pl.nb == 1024) st = srt_hist_launch<1024>(h, ws, n_dev, n_host, bits, s);
-  else st = srt_hist_launch<2048>(h, ws, n_dev, n_host, bits, s);
-  if (st != HL_OK) return st;
-  return hl_sort_passes(h, ws, n_dev, n_host, bits, s, out_k, out_v);
+  hl_sort_src src{};
+  src.k = ws.k0;
+  return srt_run(h, ws, src, n_dev, n_host, bits, s, out_k, out_v);
+}
+
+hl_status hl_sort_codes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int bits, hipStream_t s,
+                        uint32_t** out_k, uint32_t** out_v) {
+  return srt_run(h, ws, src, nullptr, n, bits, s, out_k, out_v);
 }

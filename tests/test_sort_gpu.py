@@ -1,0 +1,68 @@
+"""The general grouping's sort at the sizes and layouts where its branches
+switch: tiles of 1, 2, 4 and 8 items per thread (128 tiles of each), the last
+tile and the last group of 8 tiles full or nearly empty, digit widths on either
+side of each bin count, two and three passes, and the ways a tile finds its
+lookups' bags (one lookup per bag, a window of bags around the average position,
+a search over all bags).  Checked against numpy's stable order of the keys."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2204_05436_amd import hotline as hl
+from parity_lib import check_grouping
+
+pytestmark = pytest.mark.gpu
+
+
+def _lens(rng, layout, n):
+    """Bag lengths that add up to n."""
+    if layout == "even":  # about 3 lookups a bag
+        nb = max(1, n // 3)
+        return rng.multinomial(n, np.full(nb, 1.0 / nb))
+    if layout == "one":
+        return np.ones(n, np.int64)
+    if layout == "as_many":  # as many lookups as bags, not one each
+        lens = np.ones(n, np.int64)
+        lens[n // 2], lens[n // 2 + 1:n // 2 + 4] = 4, 0
+        return lens
+    if layout == "head":  # nearly all lookups in the first bag, thousands of empty bags, then single lookups
+        k = min(5, n - 1)
+        return np.concatenate([[n - k], np.zeros(9000, np.int64), np.ones(k, np.int64)])
+    if layout == "tail":  # the other way round
+        k = min(5, n - 1)
+        return np.concatenate([np.ones(k, np.int64), np.zeros(9000, np.int64), [n - k]])
+    raise ValueError(layout)
+
+
+@pytest.mark.parametrize("n,layout,bits", [
+    (1, "even", 10), (1023, "even", 9), (1025, "tail", 17), (8 * 1024, "head", 16), (8 * 1024 + 1, "even", 18),
+    (9001, "one", 19), (9002, "as_many", 20), (20000, "head", 22), (20000, "tail", 24),
+    (128 * 1024, "even", 18), (128 * 1024 + 1, "even", 20), (128 * 2048 + 1, "tail", 21), (128 * 2048, "one", 22),
+    (128 * 4096, "head", 17), (128 * 4096 + 1, "even", 23), (128 * 4096 + 3, "as_many", 22),
+    (128 * 8192 + 5, "even", 12)])
+def test_grouping_sort(n, layout, bits):
+    rng = np.random.default_rng(n + bits)
+    lens = _lens(rng, layout, n)
+    nb = lens.size
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    assert ptr[-1] == n
+    n_hot, k_cap = 300, 400
+    cap = (1 << bits) - 1 - n_hot  # the keys' width: bit length of n_hot + cap
+    h = hl.hl_create(np.array([1000], np.uint32), 4, "f32", k_cap)
+    try:
+        hl.hl_set_hot(h, torch.arange(n_hot, dtype=torch.int32, device="cuda"), n_hot)
+        hot = rng.zipf(1.3, n) % n_hot
+        cold = k_cap + np.where(rng.random(n) < 0.5, rng.integers(0, cap, n), rng.zipf(1.2, n) % cap)
+        codes = np.where(rng.random(n) < 0.6, hot, cold).astype(np.int32)
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, nb, nb), dtype=torch.uint8, device="cuda")
+        dc, dp = torch.from_numpy(codes).cuda(), torch.from_numpy(ptr).cuda()
+        keys, bags = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+        bag_of = np.repeat(np.arange(nb, dtype=np.uint32), lens)
+        for again in range(2):  # (the counters and published words of a call must not outlive it)
+            hl.hl_embbag_bwd_plan(h, cap, dc, dp, nb, 1, n, None, None, nb, ws)
+            hl.hl_embbag_bwd_grouping(h, cap, nb, 1, n, ws, keys, bags)
+            check_grouping(keys.cpu().numpy().view(np.uint32), bags.cpu().numpy().view(np.uint32), codes, bag_of, n_hot,
+                           k_cap, f"{layout} {n}")
+        assert hl.hl_last_device_error(h) == 0
+    finally:
+        h.close()
