@@ -29,6 +29,7 @@
 #define RB_WAVES 2  // waves per reduction block (2 measured fastest: a block waits for its slowest wave)
 #endif
 #define RB_BLOCK (RB_WAVES * 64)
+static_assert(RB_WAVES >= 2, "bw_r2_longs");
 
 // ----------------------------------------------------------------------------- row I/O
 template <int VEC, bool BF>
@@ -982,12 +983,15 @@ bw_reduce1(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals,
 // Segments spanning tiles: the tile where a segment starts (flag L) sums its
 // own piece and the next tiles' first pieces up to the first tile that is not
 // wholly inside the segment.  Piece p is summed by group p % groups in
-// ascending p, then groups are added in order.  The loads that need nothing
-// but the tile index (its flag, key and piece, the next tiles' flags) are
-// issued together, and the row with the pieces of the later tiles, so a
-// segment takes two dependent rounds of loads.
+// ascending p, then groups are added in order (so a segment of at most `groups`
+// pieces in plain ascending order).
+//
+// A segment by the whole block: its loads that need nothing but the tile index
+// (its key and piece, the next tiles' flags) are issued together, and the row
+// with the pieces of the later tiles.  Nothing is done for one of at most `most`
+// pieces.  Every thread of the block calls it.
 template <int VEC, bool BF, bool SPLIT>
-__device__ __forceinline__ void bw_reduce2_body(uint32_t t, uint32_t n_tiles, eb_geom g, void* w_hot, void* stg,
+__device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t most, uint32_t n_tiles, eb_geom g, void* w_hot, void* stg,
                                                 uint32_t n_hot, float lr, const float* __restrict__ tfirst,
                                                 const float* __restrict__ tlast, const uint32_t* __restrict__ tflag,
                                                 const uint32_t* __restrict__ tkey, float* __restrict__ gc,
@@ -1002,7 +1006,6 @@ __device__ __forceinline__ void bw_reduce2_body(uint32_t t, uint32_t n_tiles, eb
   const int32_t colv = blockIdx.y * 64 + gl;
   const bool cact = gact && colv < g.vpr;
   const int64_t col = (int64_t)colv * VEC;
-  const uint32_t f = tflag[t];
   const uint32_t key = tkey[t];
   const uint32_t t2 = t + 1 + threadIdx.x;
   const uint32_t f2 = t2 < n_tiles ? tflag[t2] : GF_W;
@@ -1012,7 +1015,6 @@ __device__ __forceinline__ void bw_reduce2_body(uint32_t t, uint32_t n_tiles, eb
   if (grp == 0 && cact) ld_f32<VEC>(tlast + (int64_t)t * g.D + col, v0);
   if (threadIdx.x == 0) s_end = n_tiles;
   __syncthreads();
-  if (!(f & GF_L)) return;  // (the same for every thread of the block)
   // the row, for group 0 (its address needs only the key)
   const bool defer = SPLIT && bw_deferred(key, n_hot, gc_rows);
   float wv[VEC];
@@ -1024,12 +1026,14 @@ __device__ __forceinline__ void bw_reduce2_body(uint32_t t, uint32_t n_tiles, eb
   __syncthreads();
   uint32_t tend = s_end;
   for (uint32_t base = t + 1 + RB_BLOCK; tend == n_tiles && base < n_tiles; base += RB_BLOCK) {
+    __syncthreads();  // (every thread has read s_end before any lowers it)
     const uint32_t t3 = base + threadIdx.x;
     if (t3 < n_tiles && !(tflag[t3] & GF_W)) atomicMin(&s_end, t3);
     __syncthreads();
     tend = s_end;
   }
   const uint32_t npieces = (tend < n_tiles ? tend : n_tiles - 1) - t + 1;
+  if (npieces <= most) return;  // (the same for every thread of the block)
   if (gact) {
     float acc[VEC];
 #pragma unroll
@@ -1069,6 +1073,110 @@ __device__ __forceinline__ void bw_reduce2_body(uint32_t t, uint32_t n_tiles, eb
 #pragma unroll
     for (int e = 0; e < VEC; ++e) wv[e] -= lr * acc[e];
     RowIO<VEC, BF>::store(rp, wv);
+  }
+}
+
+// Nearly every tile ends inside a segment, and nearly every segment ends in the
+// next tile or soon after.  So a row group finishes a segment of up to R2_SHORT
+// pieces by itself: its tile's flag, key and piece, the next tiles' flags and the
+// next piece in one round of loads, the row and any further pieces in a second.
+// A longer segment lies wholly over more than R2_SHORT - 2 tiles, so one of every
+// R2_SHORT - 1 tiles is inside it: the launch's first blocks look at those tiles,
+// and the one at the first such tile of a segment finds its start among the tiles
+// before and takes it with the whole block.  Bound by latency: a block per tile,
+// with three barriers before its store, took 7.5 us for 4,438 tiles and 13.4 for
+// 17,750 (f32 rows of 64), 9.2 for 6,828 with a run over 150 of them (bf16 rows
+// of 128); 5.4, 7.5 and 8.7 like this (the long ones one after another in the
+// blocks that met them: 5.8, 8.2 and 10.4).
+#define R2_SHORT 8
+// blocks that look for long segments, and all blocks, for n_tiles tiles (at
+// least two row groups to a block: RB_WAVES)
+__host__ __device__ __forceinline__ uint32_t bw_r2_longs(uint32_t n_tiles, const eb_geom& g) {
+  const uint32_t ngb = RB_WAVES * (uint32_t)g.NG, most = ngb < R2_SHORT ? ngb : R2_SHORT;
+  return n_tiles ? (n_tiles - 1) / (most - 1) : 0;
+}
+__host__ __device__ __forceinline__ uint32_t bw_r2_blocks(uint32_t n_tiles, const eb_geom& g) {
+  const uint32_t ngb = RB_WAVES * (uint32_t)g.NG;
+  return bw_r2_longs(n_tiles, g) + (n_tiles + ngb - 1) / ngb;
+}
+template <int VEC, bool BF, bool SPLIT>
+__device__ __forceinline__ void bw_reduce2_body(uint32_t bid, uint32_t n_tiles, eb_geom g, void* w_hot, void* stg,
+                                                uint32_t n_hot, float lr, const float* __restrict__ tfirst,
+                                                const float* __restrict__ tlast, const uint32_t* __restrict__ tflag,
+                                                const uint32_t* __restrict__ tkey, float* __restrict__ gc,
+                                                uint32_t gc_rows) {
+  typedef typename RowIO<VEC, BF>::T T;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int gi = lane / g.G, gl = lane - gi * g.G;
+  const int grp = w * g.NG + gi, ngb = RB_WAVES * g.NG;
+  const int32_t colv = blockIdx.y * 64 + gl;
+  const bool cact = gi < g.NG && colv < g.vpr;
+  const int64_t col = (int64_t)colv * VEC;
+  const uint32_t most = ngb < R2_SHORT ? ngb : R2_SHORT;
+  const uint32_t longs = bw_r2_longs(n_tiles, g);
+  if (bid < longs) {
+    const uint32_t step = most - 1, a = (bid + 1) * step;
+    uint32_t fb[R2_SHORT];  // flags of tiles a, a - 1, ..., a - step
+#pragma unroll
+    for (int i = 0; i < R2_SHORT; ++i) fb[i] = tflag[a - min((uint32_t)i, step)];
+    if (!(fb[0] & GF_W)) return;
+    uint32_t back = 0;  // the segment's start, if no earlier looked-at tile is inside it
+#pragma unroll
+    for (int i = R2_SHORT - 1; i > 0; --i)
+      if (i <= (int)step && !(fb[i] & GF_W)) back = i;
+    if (back != 0)
+      bw_reduce2_long<VEC, BF, SPLIT>(a - back, most, n_tiles, g, w_hot, stg, n_hot, lr, tfirst, tlast, tflag, tkey, gc,
+                                      gc_rows);
+    return;
+  }
+  const uint32_t t = (bid - longs) * (uint32_t)ngb + grp;
+  const bool in = gi < g.NG && t + 1 < n_tiles;  // (no segment starts in the last tile and goes on)
+  uint32_t f = 0, key = 0, nf[R2_SHORT - 1];
+  float acc[VEC], v1[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    acc[e] = 0.f;
+    v1[e] = 0.f;
+  }
+  if (in) {
+    f = tflag[t];
+    key = tkey[t];
+#pragma unroll
+    for (int i = 0; i < R2_SHORT - 1; ++i) nf[i] = tflag[min(t + 1 + i, n_tiles - 1)];
+    if (cact) {
+      ld_f32<VEC>(tlast + (int64_t)t * g.D + col, acc);
+      ld_f32<VEC>(tfirst + (int64_t)(t + 1) * g.D + col, v1);
+    }
+  }
+  if (in && (f & GF_L)) {
+    // pieces: this tile's and those up to the first tile not wholly inside
+    uint32_t np = 0;
+#pragma unroll
+    for (int i = R2_SHORT - 2; i >= 0; --i)
+      if (!(nf[i] & GF_W) || t + 1 + i == n_tiles - 1) np = i + 2;
+    if (np != 0 && np <= most && cact) {
+      const bool defer = SPLIT && bw_deferred(key, n_hot, gc_rows);
+      T* rp = bw_row<VEC, BF>(w_hot, stg, n_hot, g.D, key) + col;
+      float wv[VEC];
+      if (!defer) RowIO<VEC, BF>::load(rp, wv);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[e] = 0.f + acc[e];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[e] += v1[e];
+      for (uint32_t p = 2; p < np; ++p) {
+        float v[VEC];
+        ld_f32<VEC>(tfirst + (int64_t)(t + p) * g.D + col, v);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] += v[e];
+      }
+      if (defer) {
+        st_f32<VEC>(gc + (int64_t)(key - n_hot) * g.D + col, acc);
+      } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) wv[e] -= lr * acc[e];
+        RowIO<VEC, BF>::store(rp, wv);
+      }
+    }
   }
 }
 
@@ -1266,7 +1374,7 @@ eb_fwd_tail(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals
 }
 
 // The cold half of the forward and the backward's segments that span tiles
-// (bw_reduce2, split form) in one launch: blocks [0, n_tiles) take the
+// (bw_reduce2, split form) in one launch: the first blocks take the
 // segments, the others the sorted tail.  They share no data (the segments
 // write hot rows and staging-row sums, the tail reads staging rows and
 // writes pooled outputs).
@@ -1278,12 +1386,13 @@ eb_tail_r2(uint32_t n_tiles, void* w_hot, uint32_t n_hot, float lr, const float*
            const uint32_t* __restrict__ vals, uint32_t n, const uint32_t* __restrict__ bnd, eb_geom g, void* stg,
            int32_t stg_rows, uint32_t k_cap, const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr,
            float* __restrict__ out, uint32_t* err) {
-  if (blockIdx.x < n_tiles) {
+  const uint32_t r2 = bw_r2_blocks(n_tiles, g);
+  if (blockIdx.x < r2) {
     bw_reduce2_body<VEC, BF, true>(blockIdx.x, n_tiles, g, w_hot, stg, n_hot, lr, tfirst, tlast, tflag, tkey, gc,
                                    gc_rows);
     return;
   }
-  eb_tail_body<VEC, BF, RB_WAVES>(blockIdx.x - n_tiles, gridDim.x - n_tiles, keys, vals, n, bnd, g, stg, stg_rows,
+  eb_tail_body<VEC, BF, RB_WAVES>(blockIdx.x - r2, gridDim.x - r2, keys, vals, n, bnd, g, stg, stg_rows,
                                   n_hot, k_cap, codes, bag_ptr, out, err);
 }
 
@@ -1298,12 +1407,13 @@ eb_bags_r2(uint32_t n_tiles, void* w_hot, uint32_t n_hot, float lr, const float*
            float* __restrict__ gc, uint32_t gc_rows, eb_geom g, void* stg, int32_t stg_rows, uint32_t k_cap,
            const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr, int32_t bps, int32_t n_samples,
            float* __restrict__ out, uint32_t* err) {
-  if (blockIdx.x < n_tiles) {
+  const uint32_t r2 = bw_r2_blocks(n_tiles, g);
+  if (blockIdx.x < r2) {
     bw_reduce2_body<VEC, BF, true>(blockIdx.x, n_tiles, g, w_hot, stg, n_hot, lr, tfirst, tlast, tflag, tkey, gc,
                                    gc_rows);
     return;
   }
-  eb_fwd_body<VEC, BF, 2>(blockIdx.x - n_tiles, gridDim.x - n_tiles, w_hot, stg, stg_rows, n_hot, k_cap, codes,
+  eb_fwd_body<VEC, BF, 2>(blockIdx.x - r2, gridDim.x - r2, w_hot, stg, stg_rows, n_hot, k_cap, codes,
                           bag_ptr, bps, nullptr, nullptr, n_samples, out, g, n_samples, 1, err);
 }
 
@@ -1416,18 +1526,18 @@ template <int VEC, bool BF>
 static void launch_bwd(const hl_handle* h, uint32_t tiles, hipStream_t s, const uint32_t* sk, const uint32_t* sv,
                        uint32_t n, const float* dY, eb_geom g, void* w_hot, void* stg, uint32_t n_hot, float lr,
                        bw_ws& ws, int part) {
-  const dim3 grid(tiles, g.cchunks);
+  const dim3 grid(tiles, g.cchunks), grid2(bw_r2_blocks(tiles, g), g.cchunks);
   if (part == 0) {
     HL_KERNEL(h, s, "bw_reduce1", (bw_reduce1<VEC, BF, false>), grid, dim3(RB_BLOCK), 0, s, sk, sv, n, dY, g,
               w_hot, stg, n_hot, lr, ws.tfirst, ws.tlast, ws.tflag, ws.tkey, ws.gc, ws.gc_rows, ws.bnd, hl_hook{});
-    HL_KERNEL(h, s, "bw_reduce2", (bw_reduce2<VEC, BF, false>), grid, dim3(RB_BLOCK), 0, s, tiles, g, w_hot, stg,
+    HL_KERNEL(h, s, "bw_reduce2", (bw_reduce2<VEC, BF, false>), grid2, dim3(RB_BLOCK), 0, s, tiles, g, w_hot, stg,
               n_hot, lr, ws.tfirst, ws.tlast, ws.tflag, ws.tkey, ws.gc, ws.gc_rows);
   } else if (part == 1 || part == 3) {
     HL_KERNEL(h, s, "bw_reduce1", (bw_reduce1<VEC, BF, true>), grid, dim3(RB_BLOCK), 0, s, sk, sv, n, dY, g,
               w_hot, stg, n_hot, lr, ws.tfirst, ws.tlast, ws.tflag, ws.tkey, ws.gc, ws.gc_rows, ws.bnd,
               part == 3 ? hl_hook_take(h) : hl_hook{});
     if (part == 1)
-      HL_KERNEL(h, s, "bw_reduce2", (bw_reduce2<VEC, BF, true>), grid, dim3(RB_BLOCK), 0, s, tiles, g, w_hot, stg,
+      HL_KERNEL(h, s, "bw_reduce2", (bw_reduce2<VEC, BF, true>), grid2, dim3(RB_BLOCK), 0, s, tiles, g, w_hot, stg,
                 n_hot, lr, ws.tfirst, ws.tlast, ws.tflag, ws.tkey, ws.gc, ws.gc_rows);
   } else {
     // the tail (cold lookups: about a tenth of a mini-batch here) is a part of
@@ -1738,11 +1848,11 @@ hl_status hl_embbag_finish_cold(hl_handle* h, void* w_hot, void* staging, int32_
 #define FIN(V, B)                                                                                                   \
   do {                                                                                                             \
     if (multi)                                                                                                     \
-      HL_KERNEL(h, s, "eb_bags_r2", (eb_bags_r2<V, B>), dim3(tiles + fb, g.cchunks), dim3(RB_BLOCK), 0, s, tiles,  \
+      HL_KERNEL(h, s, "eb_bags_r2", (eb_bags_r2<V, B>), dim3(bw_r2_blocks(tiles, g) + fb, g.cchunks), dim3(RB_BLOCK), 0, s, tiles,  \
                 w_hot, h->n_hot, lr, ws.tfirst, ws.tlast, ws.tflag, ws.tkey, ws.gc, ws.gc_rows, g, staging,        \
                 stg_rows, h->k_cap, codes, bag_ptr, bps, n_samples, out, h->d_err);                                \
     else                                                                                                           \
-      HL_KERNEL(h, s, "eb_tail_r2", (eb_tail_r2<V, B>), dim3(tiles + tb, g.cchunks), dim3(RB_BLOCK), 0, s, tiles,  \
+      HL_KERNEL(h, s, "eb_tail_r2", (eb_tail_r2<V, B>), dim3(bw_r2_blocks(tiles, g) + tb, g.cchunks), dim3(RB_BLOCK), 0, s, tiles,  \
                 w_hot, h->n_hot, lr, ws.tfirst, ws.tlast, ws.tflag, ws.tkey, ws.gc, ws.gc_rows, sk, sv, n, ws.bnd, \
                 g, staging, stg_rows, h->k_cap, codes, bag_ptr, out, h->d_err);                                    \
     HL_KERNEL(h, s, "bw_cold", (bw_cold<V, B>), dim3(cb, g.cchunks), dim3(256), 0, s, sk, n, g, staging, h->n_hot, \
