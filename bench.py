@@ -63,6 +63,8 @@ def kernel_bytes(name, st, alone=False):
             "eb_fwd_gt": 4 * L + 4 * (nb + 1) + U * R + nb * O + 12 * L,
             "srt_count": 4 * L,
             "srt_pass": 16 * L,
+            # a pass with its share of the forward (half of it: two passes)
+            "eb_fwd_srt": 16 * L + (4 * L + 4 * (nb + 1) + U * R + nb * O) / 2,
             # reduction: sorted keys and bags, dY, each updated row read and written
             "bw_reduce1": 8 * L + nb * O + 2 * U * R,
         }.get(name)
@@ -430,7 +432,7 @@ def main():
 
     # the embedding forward and backward: their kernels' time per step (the
     # grouping included), against the algorithmic bytes of both passes
-    fb_kernels = ("eb_fwd", "eb_fwd_gt", "eb_fwd_hot", "eb_fwd_tail", "eb_tail_r2", "eb_bags_r2", "bw_prep",
+    fb_kernels = ("eb_fwd", "eb_fwd_gt", "eb_fwd_srt", "eb_fwd_hot", "eb_fwd_tail", "eb_tail_r2", "eb_bags_r2", "bw_prep",
                   "srt_count", "srt_pass", "gt_prep", "gt_sort", "bw_reduce1", "bw_reduce2", "bw_cold")
     t_fb = sum(kernels[n]["ms_per_step"] for n in fb_kernels if n in kernels)
     t_fb_alone = sum(kernels_alone[n]["ms_per_step"] for n in fb_kernels if n in kernels_alone)

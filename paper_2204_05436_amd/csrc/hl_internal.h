@@ -419,8 +419,22 @@ struct hl_sort_src {
   uint32_t sv;
   hl_cg_fused cf;
 };
+// The forward over every sample, run in the launches of a sort's passes by the
+// blocks past the sort's own (hl_fwd_sort.h; hl_fwd_sort_side gives `passes` for
+// a row type and lane width, NULL if there is none).
+struct hl_sort_side {
+  void (*passes)(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int npasses, int b, int nb, int items,
+                 hipStream_t s, const hl_sort_side& side);
+  const void *w_hot, *stg;
+  int32_t n_samples, bps;
+  int64_t n_lookups;
+  float* out;
+  int vec;
+};
+typedef decltype(hl_sort_side::passes) hl_sort_side_fn;
+hl_sort_side_fn hl_fwd_sort_side(bool bf16, int vec);
 hl_status hl_sort_codes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int bits, hipStream_t s,
-                        uint32_t** out_k, uint32_t** out_v);
+                        uint32_t** out_k, uint32_t** out_v, const hl_sort_side* side = nullptr);
 // Compute units in a stream's mask (0 if it cannot be read).
 int hl_stream_cus(hipStream_t s);
 
