@@ -224,40 +224,49 @@ __device__ __forceinline__ bool eb_code_row(uint32_t cu, uint32_t n_hot, uint32_
   return false;
 }
 
-// acc += the bag's rows of one kind (hot, or staging when COLD), in CSR order.
-// Invalid codes are flagged by the hot pass only.  Called by a whole row
-// group at once (its G lanes in the same control flow).  Row groups of 8 lanes
-// or more load the codes of G lookups at once, one per lane, and take the row
-// indices from each other by shuffles, 8 rows in flight; narrower groups load
-// 4 codes, then 4 rows, at a time.  Either way each lane adds the rows in CSR
-// order.
-template <int VEC, bool BF, bool COLD>
-__device__ __forceinline__ void eb_pass4(float* acc, const typename RowIO<VEC, BF>::T* w_hot,
+enum { EB_HOT_ROWS, EB_STG_ROWS, EB_ANY_ROWS };
+
+// The narrow form (row groups of fewer than 8 lanes), 4 codes and then their 4
+// rows at a time: the bag's rows of the kind asked for, hot ones added to acc_h,
+// staging ones to acc_c, each in CSR order; *anyc: some staging row was found
+// (for EB_HOT_ROWS: some hot one).  Codes that name no row are flagged except by
+// the staging pass.
+template <int VEC, bool BF, int KIND>
+__device__ __forceinline__ void eb_pass4(float* acc_h, float* acc_c, bool* anyc,
+                                         const typename RowIO<VEC, BF>::T* w_hot,
                                          const typename RowIO<VEC, BF>::T* stg, int32_t stg_rows, uint32_t n_hot,
                                          uint32_t k_cap, const int32_t* __restrict__ codes, int32_t lo, int32_t hi,
-                                         eb_geom g, int64_t col, bool cact, int gl, uint32_t* err, bool* any) {
+                                         eb_geom g, int64_t col, bool cact, int gl, uint32_t* err) {
   for (int32_t i = lo; i < hi; i += 4) {
     uint32_t cc[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) cc[k] = i + k < hi ? (uint32_t)codes[i + k] : 0u;
     float v[4][VEC];
-    bool use[4];
+    bool use[4], cold[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       int64_t r = 0;
       bool st = false;
       const bool in = i + k < hi;
       const bool ok = in && eb_code_row(cc[k], n_hot, k_cap, stg_rows, &r, &st);
-      use[k] = ok && st == COLD;
-      *any = *any || use[k];
-      if (use[k] && cact) RowIO<VEC, BF>::load((COLD ? stg : w_hot) + r * g.D + col, v[k]);
-      if (!COLD && in && !ok && gl == 0) hl_flag(err, HL_DEVERR_BAD_CODE);
+      use[k] = ok && (KIND == EB_ANY_ROWS || st == (KIND == EB_STG_ROWS));
+      cold[k] = st;
+      *anyc = *anyc || (use[k] && (KIND == EB_HOT_ROWS || st));
+      if (use[k] && cact)
+        RowIO<VEC, BF>::load((KIND == EB_STG_ROWS || (KIND == EB_ANY_ROWS && st) ? stg : w_hot) + r * g.D + col, v[k]);
+      if (KIND != EB_STG_ROWS && in && !ok && gl == 0) hl_flag(err, HL_DEVERR_BAD_CODE);
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (use[k] && cact)
+      if (use[k] && cact) {
+        if (KIND == EB_STG_ROWS || (KIND == EB_ANY_ROWS && cold[k])) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[e] += v[k][e];
+          for (int e = 0; e < VEC; ++e) acc_c[e] += v[k][e];
+        } else {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc_h[e] += v[k][e];
+        }
+      }
   }
 }
 
@@ -265,56 +274,85 @@ __device__ __forceinline__ void eb_pass4(float* acc, const typename RowIO<VEC, B
 #define EB_SEG_ROWS 8  // rows in flight per lane in the passes' wide form
 #endif
 
-// The wide form's segment: the codes of lookups b0 .. b0 + G - 1 of [b0, hi),
-// one per lane of the group (an invalid code past hi; a lane's own code that
-// names no row is flagged when `flag`).
-__device__ __forceinline__ uint32_t eb_seg_code(const int32_t* __restrict__ codes, int32_t b0, int32_t hi, int gl,
-                                                uint32_t n_hot, uint32_t k_cap, int32_t stg_rows, bool flag,
+// The wide form's segment: lane gl's lookup b0 + gl of [b0, hi) as the address of
+// its row with EB_USED (a row of the kind asked for: hot, staging, or any) and
+// EB_STG (a staging row) in bits no address has, 0 for none (past hi, another
+// kind, or a code that names no row: flagged when `flag`).  Worked out once per
+// lookup, by its own lane, and passed to the group's lanes by shuffles.
+#define EB_USED (1ull << 63)
+#define EB_STG (1ull << 62)
+template <int VEC, bool BF, int KIND>
+__device__ __forceinline__ uint64_t eb_seg_addr(const typename RowIO<VEC, BF>::T* w_hot,
+                                                const typename RowIO<VEC, BF>::T* stg,
+                                                const int32_t* __restrict__ codes, int32_t b0, int32_t hi, int gl,
+                                                uint32_t n_hot, uint32_t k_cap, int32_t stg_rows, eb_geom g, bool flag,
                                                 uint32_t* err) {
   const int32_t i = b0 + gl;
-  if (i >= hi) return ~0u;
-  const uint32_t c = (uint32_t)codes[i];
-  int64_t r;
-  bool st;
-  if (flag && !eb_code_row(c, n_hot, k_cap, stg_rows, &r, &st)) hl_flag(err, HL_DEVERR_BAD_CODE);
-  return c;
+  if (i >= hi) return 0;
+  int64_t r = 0;
+  bool st = false;
+  if (!eb_code_row((uint32_t)codes[i], n_hot, k_cap, stg_rows, &r, &st)) {
+    if (flag) hl_flag(err, HL_DEVERR_BAD_CODE);
+    return 0;
+  }
+  if (KIND == EB_HOT_ROWS ? st : (KIND == EB_STG_ROWS ? !st : false)) return 0;
+  return (uint64_t)((KIND == EB_STG_ROWS || (KIND == EB_ANY_ROWS && st) ? stg : w_hot) + r * g.D) | EB_USED |
+         (st ? EB_STG : 0ull);
+}
+
+// The rows of a segment's lookups k0 .. k0 + EB_SEG_ROWS - 1 for this lane:
+// addresses from the group's lanes (first lane g0), all loads in flight
+// together.  An address past the segment's n lookups repeats the last one's
+// and is not used.
+template <int VEC, bool BF>
+__device__ __forceinline__ void eb_seg_rows(uint64_t mine, int g0, int k0, int n, int64_t col, bool cact,
+                                            uint32_t (&fl)[EB_SEG_ROWS],
+                                            typename RowIO<VEC, BF>::Raw (&rv)[EB_SEG_ROWS]) {
+  typedef typename RowIO<VEC, BF>::T T;
+#pragma unroll
+  for (int k = 0; k < EB_SEG_ROWS; ++k) {
+    const int src = g0 + min(k0 + k, n - 1);
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)mine, src), hi = (uint32_t)__shfl((int)(mine >> 32), src);
+    fl[k] = k0 + k < n && cact ? hi : 0u;
+    if (fl[k] & (uint32_t)(EB_USED >> 32))
+      rv[k] = RowIO<VEC, BF>::load_raw(
+          reinterpret_cast<const T*>(((uint64_t)(hi & ~(uint32_t)((EB_USED | EB_STG) >> 32)) << 32) | lo) + col);
+  }
 }
 
 // acc += the bag's rows of one kind (hot, or staging when COLD), in CSR order;
-// *any: some row of that kind was found.  Invalid codes are flagged by the hot
-// pass only.  Called by a whole row group at once (its G lanes in the same
-// control flow).  Row groups of 8 lanes or more load the codes of G lookups at
-// once, one per lane, and take them from each other by shuffles, 8 rows in
-// flight; narrower groups load 4 codes, then 4 rows, at a time.  Either way
-// each lane adds the rows in CSR order.
+// *any: some row of that kind was found (on lanes that hold columns).  Invalid
+// codes are flagged by the hot pass only.  Called by a whole row group at once
+// (its G lanes in the same control flow).  Row groups of 8 lanes or more take the
+// wide form's segments of G lookups, 8 rows in flight; narrower groups load 4
+// codes, then 4 rows, at a time.  Either way each lane adds the rows in CSR
+// order.
 template <int VEC, bool BF, bool COLD>
 __device__ __forceinline__ void eb_pass(float* acc, const typename RowIO<VEC, BF>::T* w_hot,
                                         const typename RowIO<VEC, BF>::T* stg, int32_t stg_rows, uint32_t n_hot,
                                         uint32_t k_cap, const int32_t* __restrict__ codes, int32_t lo, int32_t hi,
                                         eb_geom g, int64_t col, bool cact, int gl, uint32_t* err, bool* any) {
   if (g.G < EB_SEG_ROWS) {
-    eb_pass4<VEC, BF, COLD>(acc, w_hot, stg, stg_rows, n_hot, k_cap, codes, lo, hi, g, col, cact, gl, err, any);
+    float other[VEC];
+    bool some = false;
+    eb_pass4<VEC, BF, COLD ? EB_STG_ROWS : EB_HOT_ROWS>(COLD ? other : acc, COLD ? acc : other, &some, w_hot, stg,
+                                                        stg_rows, n_hot, k_cap, codes, lo, hi, g, col, cact, gl, err);
+    *any = *any || some;
     return;
   }
   const int g0 = (int)(threadIdx.x & 63) - gl;  // the group's first lane
   for (int32_t b0 = lo; b0 < hi; b0 += g.G) {
-    const uint32_t mine = eb_seg_code(codes, b0, hi, gl, n_hot, k_cap, stg_rows, !COLD, err);
+    const uint64_t mine = eb_seg_addr<VEC, BF, COLD ? EB_STG_ROWS : EB_HOT_ROWS>(w_hot, stg, codes, b0, hi, gl, n_hot,
+                                                                                 k_cap, stg_rows, g, !COLD, err);
     const int n = min(g.G, hi - b0);
     for (int k0 = 0; k0 < n; k0 += EB_SEG_ROWS) {
-      bool use[EB_SEG_ROWS];
+      uint32_t fl[EB_SEG_ROWS];
       typename RowIO<VEC, BF>::Raw rv[EB_SEG_ROWS];
-#pragma unroll
-      for (int k = 0; k < EB_SEG_ROWS; ++k) {
-        const uint32_t c = (uint32_t)__shfl((int)mine, g0 + min(k0 + k, n - 1));
-        int64_t r = 0;
-        bool st = false;
-        use[k] = k0 + k < n && eb_code_row(c, n_hot, k_cap, stg_rows, &r, &st) && st == COLD;
-        *any = *any || use[k];
-        if (use[k] && cact) rv[k] = RowIO<VEC, BF>::load_raw((COLD ? stg : w_hot) + r * g.D + col);
-      }
+      eb_seg_rows<VEC, BF>(mine, g0, k0, n, col, cact, fl, rv);
 #pragma unroll
       for (int k = 0; k < EB_SEG_ROWS; ++k)
-        if (use[k] && cact) {
+        if (fl[k] & (uint32_t)(EB_USED >> 32)) {
+          *any = true;
           float v[VEC];
           RowIO<VEC, BF>::unpack(rv[k], v);
 #pragma unroll
@@ -326,7 +364,11 @@ __device__ __forceinline__ void eb_pass(float* acc, const typename RowIO<VEC, BF
 
 // Both kinds at once, into separate sums (hot into acc_h, staging into acc_c,
 // each in CSR order: the sums the two single-kind passes give), with one code
-// load per segment.  *anyc: some staging row was found.
+// load per segment.  *anyc: some staging row was found.  The vector instructions
+// per row bound it as much as the loads' latency does, so a row's kind is a
+// branch that all lanes usually take the same way, not a select per element:
+// 328,000 lookups in bags of 20, bf16 rows of 128, beside the sort's
+// passes: 23 + 25 -> 16.6 + 17.2 us.
 template <int VEC, bool BF>
 __device__ __forceinline__ void eb_pass_both(float* acc_h, float* acc_c, bool* anyc,
                                              const typename RowIO<VEC, BF>::T* w_hot,
@@ -334,37 +376,38 @@ __device__ __forceinline__ void eb_pass_both(float* acc_h, float* acc_c, bool* a
                                              uint32_t k_cap, const int32_t* __restrict__ codes, int32_t lo, int32_t hi,
                                              eb_geom g, int64_t col, bool cact, int gl, uint32_t* err) {
   if (g.G < EB_SEG_ROWS) {
-    bool anyh = false;
-    eb_pass4<VEC, BF, false>(acc_h, w_hot, stg, stg_rows, n_hot, k_cap, codes, lo, hi, g, col, cact, gl, err, &anyh);
-    eb_pass4<VEC, BF, true>(acc_c, w_hot, stg, stg_rows, n_hot, k_cap, codes, lo, hi, g, col, cact, gl, err, anyc);
+    eb_pass4<VEC, BF, EB_ANY_ROWS>(acc_h, acc_c, anyc, w_hot, stg, stg_rows, n_hot, k_cap, codes, lo, hi, g, col, cact,
+                                   gl, err);
     return;
   }
   const int g0 = (int)(threadIdx.x & 63) - gl;
   for (int32_t b0 = lo; b0 < hi; b0 += g.G) {
-    const uint32_t mine = eb_seg_code(codes, b0, hi, gl, n_hot, k_cap, stg_rows, true, err);
+    const uint64_t mine = eb_seg_addr<VEC, BF, EB_ANY_ROWS>(w_hot, stg, codes, b0, hi, gl, n_hot, k_cap, stg_rows, g,
+                                                            true, err);
     const int n = min(g.G, hi - b0);
     for (int k0 = 0; k0 < n; k0 += EB_SEG_ROWS) {
-      bool use[EB_SEG_ROWS], cold[EB_SEG_ROWS];
+      uint32_t fl[EB_SEG_ROWS];
       typename RowIO<VEC, BF>::Raw rv[EB_SEG_ROWS];
+      eb_seg_rows<VEC, BF>(mine, g0, k0, n, col, cact, fl, rv);
 #pragma unroll
       for (int k = 0; k < EB_SEG_ROWS; ++k) {
-        const uint32_t c = (uint32_t)__shfl((int)mine, g0 + min(k0 + k, n - 1));
-        int64_t r = 0;
-        bool st = false;
-        use[k] = k0 + k < n && eb_code_row(c, n_hot, k_cap, stg_rows, &r, &st);
-        cold[k] = st;
-        *anyc = *anyc || (use[k] && st);
-        if (use[k] && cact) rv[k] = RowIO<VEC, BF>::load_raw((st ? stg : w_hot) + r * g.D + col);
-      }
-#pragma unroll
-      for (int k = 0; k < EB_SEG_ROWS; ++k)
-        if (use[k] && cact) {
+        const bool used = fl[k] & (uint32_t)(EB_USED >> 32), cold = fl[k] & (uint32_t)(EB_STG >> 32);
+        if (used && !cold) {
           float v[VEC];
           RowIO<VEC, BF>::unpack(rv[k], v);
-          float* a = cold[k] ? acc_c : acc_h;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) a[e] += v[e];
+          for (int e = 0; e < VEC; ++e) acc_h[e] += v[e];
         }
+        if (__ballot(cold) != 0) {  // (rare: most rows are hot)
+          if (cold) {
+            *anyc = true;
+            float v[VEC];
+            RowIO<VEC, BF>::unpack(rv[k], v);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc_c[e] += v[e];
+          }
+        }
+      }
     }
   }
 }
