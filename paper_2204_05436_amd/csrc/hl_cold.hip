@@ -3,16 +3,15 @@
 // the pinned host table by the GPU over the host link, with the lookups'
 // codes pointed at the staging rows.
 //
-//   insert : a block per 256 bags; each round a wave compacts its cold
-//            lookups (code -1, sample selected) so that a lane handles about
-//            one, which enters an open-addressing hash table keyed by row id
-//            with one CAS (a 64-bit atomic min keeps the smallest lookup index
-//            per id); the block lists its cold lookups in its own lookup range
-//   rank   : a scan over all lookups in index order (tiles of 2048, decoupled
-//            look-back read by the whole block) numbers the first occurrences:
-//            staging row u of each id
-//   codes  : capacity check, code rewrite, the cold id list, and the clearing
-//            of the table slots this call used
+//   insert : each cold lookup (code -1) of a selected sample enters an
+//            open-addressing hash table keyed by row id with one CAS (a 64-bit
+//            atomic min keeps the smallest lookup index per id); a thread per
+//            lookup, or with a sample list a wave or a block per listed sample
+//   rank   : a scan over all lookups in index order (tiles of 2048, their counts
+//            published and read by the whole block) numbers the first
+//            occurrences: staging row u of each id
+//   codes  : the selected cold lookups again: capacity check, code rewrite, the
+//            cold id list, and the clearing of the table slots this call used
 //   copy   : the row copy between the pinned host table and the staging rows,
 //            in either direction (fetch before the mu-batch runs, write-back
 //            of the updated rows after it)
@@ -25,9 +24,6 @@
 
 #define CG_C_NCOLD 1
 #define CG_C_RTILE 2
-#define CG_BAGS 256      // bags per insert block (at most; fewer for bags of many lookups)
-#define CG_BAGS_MIN 64
-#define CG_IR 1024       // lookup positions per insert round (256 threads x 4)
 #define CG_RT_THREADS 512
 #define CG_RT (CG_RT_THREADS * 4)  // lookups per rank tile
 
@@ -35,12 +31,9 @@ struct cg_ws {
   uint32_t* ctr;      // header counters
   uint32_t* uidx;     // [S] staging row of the id in the slot
   uint32_t* slotof;   // [n_max] slot of a cold lookup
-  uint32_t* blist;    // [n_max] cold lookups of insert block b at [bag_ptr[b * bpb], ...)
-  uint32_t* bcnt;     // [iblocks] their number
   uint32_t* fst;      // [n_max] id of staging row u
   uint64_t* rstat;    // [rtiles] look-back status of the rank scan
-  uint8_t* mask;      // [max_samples] selected samples (when a sample list is given)
-  uint32_t S, rtiles, iblocks;
+  uint32_t S, rtiles;
 };
 
 static uint32_t cg_table_slots(uint32_t n_max) {
@@ -49,25 +42,21 @@ static uint32_t cg_table_slots(uint32_t n_max) {
   return s;
 }
 
-static void cg_carve(hl_carver& c, cg_ws& ws, uint32_t n_max, int64_t n_bags, int32_t n_samples) {
+static void cg_carve(hl_carver& c, cg_ws& ws, uint32_t n_max) {
   ws.S = cg_table_slots(n_max);
   ws.rtiles = n_max ? hl_div_up(n_max, CG_RT) : 1;
-  ws.iblocks = n_bags > 0 ? hl_div_up((uint64_t)n_bags, CG_BAGS_MIN) : 1;
   ws.ctr = c.base ? c.header() + HL_HDR_COLD : nullptr;
   ws.uidx = c.take<uint32_t>(ws.S);
   ws.slotof = c.take<uint32_t>(n_max);
-  ws.blist = c.take<uint32_t>(n_max);
-  ws.bcnt = c.take<uint32_t>(ws.iblocks);
   ws.fst = c.take<uint32_t>(n_max);
   ws.rstat = c.take<uint64_t>(ws.rtiles);
-  ws.mask = c.take<uint8_t>((size_t)n_samples + 1);
 }
 
 size_t hl_cold_ws_bytes(const hl_handle* h, int64_t max_lookups, int64_t max_bags, int32_t max_samples) {
   (void)h;
   hl_carver c = hl_carver::after_header(nullptr, 0);
   cg_ws ws;
-  cg_carve(c, ws, (uint32_t)max_lookups, max_bags, max_samples);
+  cg_carve(c, ws, (uint32_t)max_lookups);
   return c.off;
 }
 
@@ -91,103 +80,67 @@ static hl_status cg_table(hl_handle* h, uint32_t S, hipStream_t s, uint64_t** ou
   return HL_OK;
 }
 
-__global__ void cg_mask(uint8_t* mask, int32_t n_samples, const int32_t* __restrict__ ids, const int32_t* n_dev,
-                        int32_t n_max, int phase, uint32_t* err) {
-  if (phase == 0) {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_samples; i += gridDim.x * blockDim.x) mask[i] = 0;
-  } else {
-    int32_t n = n_max;
-    if (n_dev) n = min(max(*n_dev, 0), n_max);
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-      const int32_t s = ids[i];
-      if (s >= 0 && s < n_samples) mask[s] = 1;
-      else hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+// The selected lookups: of the first sel_bags bags (ids NULL), one per thread of
+// a flat grid, or of the listed samples, tps threads (64 or 256) per sample.
+// f(i, g) takes a lookup with code -1 and, when `gids` is given, its id.  One
+// lookup per thread keeps each thread to one chain of dependent accesses (probe,
+// slot, code): four per thread took 7.6 and 5.3 us (insert, codes; 212,992
+// lookups) against 4.6 and 3.3, and blocks that first compacted their cold lookups
+// in LDS 5.7 and 4.0.  A list marked in a mask over the samples by two launches of
+// its own and searched by bag: 16.7 us for the insert of 328,000 lookups in bags
+// of 20, 5.6 by the listed samples.
+struct cg_sel {
+  const int32_t* ids;     // the listed samples (NULL: every sample up to sel_bags / bps)
+  const int32_t* n_dev;   // their number on the device (NULL: n_max)
+  int32_t n_max, n_samples, bps, tps;
+  int64_t sel_bags;
+};
+template <typename F>
+__device__ __forceinline__ void cg_lookups(const cg_sel& sel, const int32_t* __restrict__ bag_ptr,
+                                           const int32_t* codes, const uint32_t* gids, uint32_t n_lookups, uint32_t* err,
+                                           F f) {
+  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
+  int64_t b0 = 0, b1 = sel.sel_bags;
+  if (sel.ids) {
+    const int32_t q = (int32_t)(t / (uint32_t)sel.tps);
+    const int32_t n = sel.n_dev ? min(max(*sel.n_dev, 0), sel.n_max) : sel.n_max;
+    if (q >= n) return;
+    const int32_t s = sel.ids[q];
+    if (s < 0 || s >= sel.n_samples) {
+      if (t % (uint32_t)sel.tps == 0) hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+      return;
     }
+    b0 = (int64_t)s * sel.bps;
+    b1 = b0 + sel.bps;
+  }
+  const uint32_t lo = (uint32_t)min(max((int64_t)bag_ptr[b0], (int64_t)0), (int64_t)n_lookups);
+  const uint32_t hi = (uint32_t)min(max((int64_t)bag_ptr[b1], (int64_t)0), (int64_t)n_lookups);
+  if (sel.ids) {
+    for (uint32_t i = lo + t % (uint32_t)sel.tps; i < hi; i += (uint32_t)sel.tps) {
+      const int32_t c = codes[i];
+      const uint32_t g = gids ? gids[i] : 0u;
+      if (c == -1) f(i, g);
+    }
+  } else if (t < n_lookups) {
+    const int32_t c = codes[t];
+    const uint32_t g = gids ? gids[t] : 0u;
+    if (c == -1 && t >= lo && t < hi) f(t, g);
   }
 }
 
 __global__ void __launch_bounds__(256)
 cg_insert(const uint32_t* __restrict__ gids, const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr,
-          int64_t n_bags, int32_t bps, int32_t bpb, const uint8_t* __restrict__ mask, uint32_t n_lookups,
-          uint64_t n_rows, uint64_t* table, cg_ws ws, uint32_t* err) {
-  __shared__ int32_t off[CG_BAGS + 1];
-  __shared__ uint32_t cl[CG_IR], cg_[CG_IR];
-  __shared__ uint32_t wn[4];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int64_t b0 = (int64_t)blockIdx.x * bpb;
-  const int nb = (int)min((int64_t)bpb, n_bags - b0);
-  for (int j = tid; j <= nb; j += 256) off[j] = bag_ptr[b0 + j];
-  __syncthreads();
-  const int32_t lo = off[0], hi = (int32_t)min((int64_t)off[nb], (int64_t)n_lookups);
+          cg_sel sel, uint32_t n_lookups, uint64_t n_rows, uint64_t* table, cg_ws ws, uint32_t* err) {
   // the rank scan's status words, cleared for the kernel that follows
-  for (uint32_t j = blockIdx.x * 256 + tid; j < ws.rtiles; j += gridDim.x * 256) ws.rstat[j] = 0;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  const uint32_t smask = ws.S - 1;
-  uint32_t listed = 0;  // block-wide count so far (uniform)
-  for (int32_t r0 = lo; r0 < hi; r0 += CG_IR) {
-    // positions r0 + k*256 + tid: cold and selected?
-    bool cold[4];
-    int32_t pos[4];
-    uint32_t gg[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {  // codes and ids loaded together
-      pos[k] = r0 + k * 256 + tid;
-      const bool in = pos[k] < hi;
-      cold[k] = in && codes[pos[k]] == -1;
-      gg[k] = in ? gids[pos[k]] : 0u;
+  for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j < ws.rtiles; j += gridDim.x * 256) ws.rstat[j] = 0;
+  cg_lookups(sel, bag_ptr, codes, gids, n_lookups, err, [&](uint32_t i, uint32_t g) {
+    if (g >= n_rows) {
+      hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+      ws.slotof[i] = 0xFFFFFFFFu;
+    } else {
+      ws.slotof[i] = hl_cg_insert(table, ws.S - 1, g, i);
     }
-    if (mask) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (!cold[k]) continue;
-        int a = 0, b = nb;
-        while (b - a > 1) {
-          const int m = (a + b) >> 1;
-          if (off[m] <= pos[k]) a = m; else b = m;
-        }
-        cold[k] = mask[(b0 + a) / bps] != 0;
-      }
-    }
-    // compact the round's cold positions into cl (wave-major, then item, then lane)
-    uint32_t c = 0;
-    uint64_t m[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      m[k] = __ballot(cold[k]);
-      c += (uint32_t)__popcll(m[k]);
-    }
-    if (lane == 0) wn[w] = c;
-    __syncthreads();
-    uint32_t base = 0, tot = 0;
-    for (int q = 0; q < 4; ++q) {
-      if (q < w) base += wn[q];
-      tot += wn[q];
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (cold[k]) {
-        cl[base + (uint32_t)__popcll(m[k] & lt)] = (uint32_t)pos[k];
-        cg_[base + (uint32_t)__popcll(m[k] & lt)] = gg[k];
-      }
-      base += (uint32_t)__popcll(m[k]);
-    }
-    __syncthreads();
-    // each thread inserts about one lookup
-    for (uint32_t e = tid; e < tot; e += 256) {
-      const uint32_t i = cl[e];
-      const uint32_t g = cg_[e];
-      if (g >= n_rows) {
-        hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
-        ws.slotof[i] = 0xFFFFFFFFu;
-        continue;
-      }
-      ws.slotof[i] = hl_cg_insert(table, smask, g, i);
-      ws.blist[lo + listed + e] = i;
-    }
-    listed += tot;
-    __syncthreads();  // cl and wn reused
-  }
-  if (tid == 0) ws.bcnt[blockIdx.x] = listed;
+  });
 }
 
 // Lookup i is a first occurrence iff it is a cold lookup of this call whose
@@ -245,9 +198,12 @@ cg_rank(const uint32_t* __restrict__ gids, const int32_t* __restrict__ codes, ui
     if (q < w) before += wt[q];
     tc += wt[q];
   }
-  if (tid == 0) hl_st_store(ws.rstat + tile, hl_st_pack(epoch, tile == 0 ? HL_ST_PRE : HL_ST_AGG, tc));
-  const uint32_t ex = tile > 0 ? hl_block_lookback(ws.rstat, tile, epoch, err) : 0u;
-  if (tid == 0 && tile > 0) hl_st_store(ws.rstat + tile, hl_st_pack(epoch, HL_ST_PRE, ex + tc));
+  const bool direct = gridDim.x <= HL_DIRECT_TILES;  // (else a look-back through inclusive prefixes)
+  if (tid == 0) hl_st_store(ws.rstat + tile, hl_st_pack(epoch, tile == 0 && !direct ? HL_ST_PRE : HL_ST_AGG, tc));
+  uint32_t ex = 0;
+  if (direct) ex = hl_block_before(ws.rstat, tile, epoch, err);
+  else if (tile > 0) ex = hl_block_lookback(ws.rstat, tile, epoch, err);
+  if (!direct && tid == 0 && tile > 0) hl_st_store(ws.rstat + tile, hl_st_pack(epoch, HL_ST_PRE, ex + tc));
   uint32_t run = ex + before;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -267,24 +223,22 @@ cg_rank(const uint32_t* __restrict__ gids, const int32_t* __restrict__ codes, ui
   }
 }
 
-// Insert block b's listed cold lookups point their codes at their staging
-// rows and free their table slots; cold_ids[u] = id of staging row u.  When
-// the rows do not fit: only the capacity bit and the slot clearing.
+// The selected cold lookups point their codes at their staging rows and free
+// their table slots; cold_ids[u] = id of staging row u.  When the rows do not
+// fit: only the capacity bit and the slot clearing.  (A sample listed twice is
+// done twice: the second time its codes are no longer -1, or are left alone.)
 __global__ void __launch_bounds__(256)
-cg_codes(const int32_t* __restrict__ bag_ptr, int32_t bpb, uint64_t* table, cg_ws ws, int32_t cap, uint32_t k_cap,
-         int32_t* __restrict__ codes, uint32_t* __restrict__ cold_ids, uint32_t* err) {
+cg_codes(const int32_t* __restrict__ bag_ptr, cg_sel sel, uint32_t n_lookups, uint64_t* table, cg_ws ws, int32_t cap,
+         uint32_t k_cap, int32_t* codes, uint32_t* __restrict__ cold_ids, uint32_t* err) {
   const uint32_t ncold = ws.ctr[CG_C_NCOLD];
   const bool fits = ncold <= (uint32_t)cap;
   if (blockIdx.x == 0 && threadIdx.x == 0 && !fits) hl_flag(err, HL_DEVERR_CAPACITY);
-  const uint32_t cnt = ws.bcnt[blockIdx.x];
-  const int32_t lo = bag_ptr[(int64_t)blockIdx.x * bpb];
-  for (uint32_t e = threadIdx.x; e < cnt; e += 256) {
-    const uint32_t i = ws.blist[lo + e];
+  cg_lookups(sel, bag_ptr, codes, nullptr, n_lookups, err, [&](uint32_t i, uint32_t) {
     const uint32_t sl = ws.slotof[i];
-    if (sl >= ws.S) continue;
+    if (sl >= ws.S) return;
     if (fits) codes[i] = (int32_t)(k_cap + ws.uidx[sl]);
     table[sl] = 0;
-  }
+  });
   if (!fits) return;
   const uint32_t gs = gridDim.x * blockDim.x;
   for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < ncold; u += gs) cold_ids[u] = ws.fst[u];
@@ -382,39 +336,28 @@ extern "C" hl_status hl_cold_plan(hl_handle* h, const uint32_t* gids, int32_t* c
   hipStream_t s = (hipStream_t)stream;
   hl_carver c = hl_carver::after_header(workspace, ws_bytes);
   cg_ws ws;
-  cg_carve(c, ws, (uint32_t)n_lookups, n_bags, n_samples);
+  cg_carve(c, ws, (uint32_t)n_lookups);
   uint64_t* table = nullptr;
   hl_status st = cg_table(h, ws.S, s, &table);
   if (st != HL_OK) return st;
   const uint32_t n = (uint32_t)n_lookups;
-  // selection: every sample (no list) or the listed ones (a mask over samples);
-  // an empty selection inserts nothing
-  const uint8_t* mask = nullptr;
-  if (sample_ids) {
-    uint32_t gb = hl_div_up(n_samples > 0 ? n_samples : 1, 256);
-    if (gb > 4096) gb = 4096;
-    HL_KERNEL(h, s, "cg_mask", cg_mask, dim3(gb), dim3(256), 0, s, ws.mask, n_samples, sample_ids, n_sel_dev,
-              n_sel_max, 0, h->d_err);
-    HL_KERNEL(h, s, "cg_mask", cg_mask, dim3(gb), dim3(256), 0, s, ws.mask, n_samples, sample_ids, n_sel_dev,
-              n_sel_max, 1, h->d_err);
-    mask = ws.mask;
-  }
-  // without a list the first n_sel_max samples are selected: their bags come first
-  const int64_t sel_bags = sample_ids ? n_bags : (int64_t)n_sel_max * bps;
-  // bags per insert block: about 2048 lookups, CG_BAGS_MIN to CG_BAGS bags
-  int32_t bpb = CG_BAGS;
-  while (bpb > CG_BAGS_MIN && (int64_t)bpb * n > 2048 * n_bags) bpb >>= 1;
-  const uint32_t ib = sel_bags > 0 ? hl_div_up((uint64_t)sel_bags, bpb) : 0;
+  // selection: the first n_sel_max samples (no list) or the listed ones; an
+  // empty selection inserts nothing
+  // (a sample of more than 64 lookups or so: a block's threads, else a wave's)
+  const int32_t tps = n_lookups > 96ll * n_samples ? 256 : 64;
+  const cg_sel sel{sample_ids, n_sel_dev, n_sel_max, n_samples, bps, tps, (int64_t)n_sel_max * bps};
+  uint32_t ib = 0;
+  if (n > 0 && n_sel_max > 0) ib = sample_ids ? hl_div_up((uint64_t)n_sel_max * tps, 256) : hl_div_up(n, 256);
   if (ib > 0)
-    HL_KERNEL(h, s, "cg_insert", cg_insert, dim3(ib), dim3(256), 0, s, gids, codes, bag_ptr, sel_bags, bps, bpb, mask,
-              n, h->n_rows, table, ws, h->d_err);
+    HL_KERNEL(h, s, "cg_insert", cg_insert, dim3(ib), dim3(256), 0, s, gids, codes, bag_ptr, sel, n, h->n_rows, table, ws,
+              h->d_err);
   // the insert kernel cleared the status words, so one fixed tag serves every
   // call (and every replay of a captured graph)
   const uint32_t epoch = 1;
   HL_KERNEL(h, s, "cg_rank", cg_rank, dim3(ws.rtiles), dim3(CG_RT_THREADS), 0, s, gids, codes, ib > 0 ? n : 0u, table, ws,
             n_cold_dev, epoch, nullptr, 0, 0, h->d_err);
   if (ib > 0)
-    HL_KERNEL(h, s, "cg_codes", cg_codes, dim3(ib), dim3(256), 0, s, bag_ptr, bpb, table, ws, cap, h->k_cap, codes,
+    HL_KERNEL(h, s, "cg_codes", cg_codes, dim3(ib), dim3(256), 0, s, bag_ptr, sel, n, table, ws, cap, h->k_cap, codes,
               cold_ids_out, h->d_err);
   HL_LAUNCHED();
   return HL_OK;
@@ -432,7 +375,7 @@ static hl_carver cg_fused_carver(const hl_handle* h, void* workspace, size_t ws_
 size_t hl_plan_ws_bytes(const hl_handle* h, int64_t max_lookups, int64_t max_bags, int32_t max_samples) {
   hl_carver c = cg_fused_carver(h, nullptr, 0, max_lookups, max_bags);
   cg_ws ws;
-  cg_carve(c, ws, (uint32_t)max_lookups, max_bags, max_samples);
+  cg_carve(c, ws, (uint32_t)max_lookups);
   return c.off;
 }
 
@@ -444,7 +387,7 @@ hl_status hl_cold_fused_begin(hl_handle* h, int64_t n_lookups, int64_t n_bags, i
   if (ws_bytes < hl_plan_ws_bytes(h, n_lookups, n_bags, n_samples)) return HL_ERR_CAPACITY;
   hl_carver c = cg_fused_carver(h, workspace, ws_bytes, n_lookups, n_bags);
   cg_ws ws;
-  cg_carve(c, ws, (uint32_t)n_lookups, n_bags, n_samples);
+  cg_carve(c, ws, (uint32_t)n_lookups);
   // no growth here: a larger table is allocated by a plain cold plan, after
   // its waits (the table is shared with the steps still in flight)
   if (h->cg_slots < ws.S || !h->cg_table) return HL_ERR_CAPACITY;

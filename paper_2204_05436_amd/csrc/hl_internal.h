@@ -484,10 +484,6 @@ __device__ __forceinline__ void hl_hook_gate(const hl_hook& k) {
   hl_hook_spin(k.wflag, k.wv, k.err);
   hl_hook_spin(k.w2flag, k.w2v, k.err);
 }
-#ifndef HL_LB_WIN
-#define HL_LB_WIN 32
-#endif
-
 __device__ __forceinline__ uint64_t hl_st_pack(uint32_t epoch, uint64_t flag, uint32_t v) {
   return ((uint64_t)epoch << 32) | (flag << 30) | (uint64_t)(v & 0x3FFFFFFFu);
 }
@@ -497,45 +493,6 @@ __device__ __forceinline__ void hl_st_store(uint64_t* p, uint64_t w) {
 __device__ __forceinline__ uint64_t hl_st_load(const uint64_t* p) {
   return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Exclusive prefix of tile `tile`'s value over tiles [0, tile) for one lane of
-// status words laid out with stride `stride` between tiles.  Reads a window of
-// HL_LB_WIN predecessors per round trip.
-__device__ __forceinline__ uint32_t hl_lookback(const uint64_t* st, uint32_t tile, size_t stride,
-                                                uint32_t epoch, uint32_t* err) {
-  uint32_t excl = 0;
-  int64_t j = (int64_t)tile - 1;
-  uint32_t spins = 0;
-  while (j >= 0) {
-    uint64_t w[HL_LB_WIN];
-#pragma unroll
-    for (int k = 0; k < HL_LB_WIN; ++k) w[k] = (j - k >= 0) ? hl_st_load(st + (size_t)(j - k) * stride) : 0ull;
-    int k = 0;
-    bool stall = false;
-#pragma unroll
-    for (int q = 0; q < HL_LB_WIN; ++q) {
-      if (stall || j - q < 0) continue;
-      const uint32_t e = (uint32_t)(w[q] >> 32);
-      const uint64_t f = (w[q] >> 30) & 3ull;
-      if (e != epoch || f == 0) {
-        stall = true;
-        continue;
-      }
-      excl += (uint32_t)(w[q] & 0x3FFFFFFFu);
-      if (f == HL_ST_PRE) return excl;
-      k = q + 1;
-    }
-    j -= k;
-    if (stall) {
-      if (++spins > HL_SPIN_LIMIT) {
-        hl_flag(err, HL_DEVERR_STALL);
-        return excl;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  }
-  return excl;
-}
-
 // Exclusive prefix of `tile` over tiles [0, tile) from single-value status
 // words (hl_st_pack), read by the whole block: thread t looks at tile j - t of
 // the current window, so one round trip covers blockDim.x predecessors, and the
@@ -585,6 +542,39 @@ __device__ __forceinline__ uint32_t hl_block_lookback(const uint64_t* st, uint32
     }
   }
   return excl;
+}
+
+// The same from words that keep their tiles' own counts (never rewritten by
+// inclusive prefixes): each thread waits for the words of its share of the
+// earlier tiles and the block adds them up, so a block waits one round trip after
+// the last of them was published, whatever their number.  Every earlier tile must
+// be running (tiles by ticket).  For launches of a few thousand tiles at most: a
+// tile reads every earlier word.
+#define HL_DIRECT_TILES 4096
+__device__ __forceinline__ uint32_t hl_block_before(const uint64_t* st, uint32_t tile, uint32_t epoch, uint32_t* err) {
+  __shared__ uint32_t s_part[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+  uint32_t v = 0, spins = 0;
+  for (uint32_t t = threadIdx.x; t < tile; t += blockDim.x) {
+    for (;;) {
+      const uint64_t wd = hl_st_load(st + t);
+      if ((uint32_t)(wd >> 32) == epoch && ((wd >> 30) & 3ull) != 0) {
+        v += (uint32_t)(wd & 0x3FFFFFFFu);
+        break;
+      }
+      if (++spins > HL_SPIN_LIMIT) {
+        hl_flag(err, HL_DEVERR_STALL);
+        break;
+      }
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if (lane == 0) s_part[w] = v;
+  __syncthreads();
+  uint32_t tot = 0;
+  for (int q = 0; q < nw; ++q) tot += s_part[q];
+  return tot;
 }
 
 // ----------------------------------------------------------------------------- misc

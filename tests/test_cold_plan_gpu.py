@@ -1,0 +1,59 @@
+"""The cold plan's selections against the oracle: every sample, the first ones,
+a list of samples (a wave or a block each; out of order, repeated, counted on
+the device), and enough lookups that the rank scan goes back to a look-back."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2204_05436_amd import hotline as hl
+from parity_lib import u32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,bps,mean,how", [
+    (1, 1, 1, "all"), (333, 5, 1, "all"), (333, 5, 3, "first"), (257, 3, 2, "list"), (257, 3, 2, "dup"),
+    (64, 8, 20, "list"), (65, 8, 20, "dup"), (1000, 26, 1, "list"), (70, 4, 0, "all"), (8_400_001, 1, 1, "all")])
+def test_cold_plan_selection(B, bps, mean, how):
+    rng = np.random.default_rng(B + bps)
+    n_bags = B * bps
+    lens = np.ones(n_bags, np.int64) if mean == 1 else rng.poisson(mean, n_bags)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(ptr[-1])
+    n_rows, k_cap = 50_000, 9_000
+    hot = np.sort(rng.permutation(n_rows)[:k_cap]).astype(np.uint32)
+    gids = (rng.zipf(1.2, n) % n_rows).astype(np.uint32)
+    codes = O.remap(hot, gids)
+    if how == "all":
+        sel, n_max, dev = np.arange(B, dtype=np.int32), B, None
+    elif how == "first":
+        sel, n_max, dev = np.arange(B // 2, dtype=np.int32), B // 2, None
+    else:
+        sel = np.sort(rng.permutation(B)[:max(1, B // 2)]).astype(np.int32)
+        n_max, dev = B, sel.size
+    want_cold, want_codes = O.cold_plan(gids, codes.copy(), ptr, sel, sel.size, bps, k_cap)
+    listed = sel
+    if how == "dup":
+        listed = rng.permutation(np.concatenate([sel, sel[: B - sel.size]])).astype(np.int32)
+        dev = listed.size
+    h = hl.hl_create(np.array([n_rows], np.uint32), 4, "f32", k_cap)
+    try:
+        d = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int32)).cuda()
+        dg, dc, dp = d(gids), d(codes.astype(np.int32)), d(ptr)
+        ids = cnt = None
+        if how in ("list", "dup"):
+            ids = d(np.concatenate([listed, np.full(B - listed.size, -7, np.int32)]))
+            cnt = torch.tensor([dev], dtype=torch.int32, device="cuda")
+        cap = max(1, n)
+        cold, nc = torch.zeros(cap, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, n_bags, B), dtype=torch.uint8, device="cuda")
+        for _ in range(2):  # (the table is left clean)
+            dc.copy_(d(codes.astype(np.int32)))
+            hl.hl_cold_plan(h, dg, dc, dp, B, bps, n, ids, cnt, n_max, cap, cold, nc, ws)
+            assert int(nc.item()) == want_cold.size
+            assert np.array_equal(u32(cold[:want_cold.size]), want_cold)
+            assert np.array_equal(dc.cpu().numpy(), want_codes)
+        assert hl.hl_last_device_error(h) == 0
+    finally:
+        h.close()
