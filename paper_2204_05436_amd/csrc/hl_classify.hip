@@ -315,22 +315,22 @@ extern "C" hl_status hl_remap(const hl_handle* h, const uint32_t* gids, int64_t 
 // table base (address generation), probes the hot-set bitmap (input
 // classifier), writes the hot slot or -1 (remap) and clears its sample's flag
 // when the row is not hot; then the popular samples of all earlier blocks,
-// obtained by decoupled look-back, place each sample in the popular or the
-// non-popular list (fragmentation, Eq. 3).  The look-back status words live in
-// the workspace header, tagged with an epoch kept on the device: the last block
-// to finish advances it, so no clearing is needed between calls (nor between
-// replays of a captured graph).
+// which each block publishes and every later one adds up, place each sample in
+// the popular or the non-popular list (fragmentation, Eq. 3).  The published
+// words live in the workspace header, tagged with an epoch kept on the device
+// beside the ticket that hands out the tiles: the block that takes the last tile
+// advances it, so no clearing is needed between calls (nor between replays of a
+// captured graph).
 #define DS_THREADS 512
 #define DS_MAX_TABLES 1024  // table bases and sizes in LDS up to this many tables
 #define DS_MAX_BAGS 4096
 #define DS_MAX_SPB 2048
-#define DS_LOOKUPS_MIN 512  // lookups per block: n_lookups / DS_BLOCKS_AIM within these bounds
-#define DS_LOOKUPS_MAX 2048
-#define DS_BLOCKS_AIM 64
+#define DS_LOOKUPS_MIN 512  // lookups per block: n_lookups / blocks aimed at, within these bounds
+#define DS_LOOKUPS_MAX 2048 // (twice that when aiming at DS_BLOCKS_WIDE)
+#define DS_BLOCKS_AIM 64    // on streams of at most DS_BLOCKS_WIDE compute units
+#define DS_BLOCKS_WIDE 160   // on others
 #define DS_MAP 8192         // lookups per block mapped to their bag in LDS
-#define DS_EPOCH 0
-#define DS_DONE 1
-#define DS_TILE 2
+#define DS_TICKET 0         // 64-bit: the call's epoch over the tiles handed out
 __global__ void __launch_bounds__(DS_THREADS)
 ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr, int32_t n_samples, int32_t bps,
           int32_t spb, const uint32_t* __restrict__ base, const uint32_t* __restrict__ nrow, int32_t n_tables,
@@ -347,9 +347,14 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
   hl_hook_head(hk);
   hl_hook_gate(hk);
   if (tid == 0) {
-    s_tile = atomicInc(hdr + DS_TILE, gridDim.x - 1);
-    // status words of earlier calls carry older epochs; zeroed words carry no flag
-    s_epoch = __hip_atomic_load(hdr + DS_EPOCH, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // one atomic hands out the tile and the call's epoch (status words of earlier
+    // calls carry older ones; zeroed words carry no flag); the block that takes
+    // the last tile resets the tiles and advances the epoch for the next call
+    unsigned long long* tk = (unsigned long long*)(hdr + DS_TICKET);
+    const unsigned long long x = atomicAdd(tk, 1ull);
+    s_tile = (uint32_t)x;
+    s_epoch = (uint32_t)(x >> 32);
+    if (s_tile == gridDim.x - 1) atomicAdd(tk, (1ull << 32) - gridDim.x);
   }
   __syncthreads();
   const uint32_t tile = s_tile, epoch = s_epoch;
@@ -459,9 +464,9 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
     if (q < w) before += wsum[q];
     tc += wsum[q];
   }
-  if (tid == 0) hl_st_store(st + tile, hl_st_pack(epoch, tile == 0 ? HL_ST_PRE : HL_ST_AGG, tc));
-  const uint32_t ex = tile > 0 ? hl_block_lookback(st, tile, epoch, err) : 0u;
-  if (tid == 0 && tile > 0) hl_st_store(st + tile, hl_st_pack(epoch, HL_ST_PRE, ex + tc));
+  if (tid == 0) hl_st_store(st + tile, hl_st_pack(epoch, HL_ST_AGG, tc));
+  static_assert(HL_DISP_MAX_TILES <= HL_DIRECT_TILES, "every tile reads the earlier ones' counts");
+  const uint32_t ex = hl_block_before(st, tile, epoch, err);
   uint32_t pp = ex + before;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -476,34 +481,39 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
     counts[0] = (int32_t)(ex + tc);
     counts[1] = n_samples - (int32_t)(ex + tc);
   }
-  // the last block to finish advances the epoch for the next call
-  if (tid == 0 && atomicInc(hdr + DS_DONE, gridDim.x - 1) == gridDim.x - 1)
-    __hip_atomic_store(hdr + DS_EPOCH, epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // the samples per block of the fused dispatch, or 0 when it takes the step by
-// step calls
+// step calls (which does not depend on cus, the compute units of the call's
+// stream).  More blocks spread the random probes (a compute unit takes one cache
+// line a cycle), but every block's ticket is an atomic on one word: 212,992
+// lookups took 12.7 us with about 64 or 96 blocks aimed at, 11.8 with 128, 11.5
+// with 160, 12.0 with 192, 12.3 with 256 (15.0 with 104 blocks, a look-back
+// through inclusive prefixes and a second counter for the call's end); batch
+// 32768 26.9 -> 20.5 with 208 blocks of 4096 lookups (416 of 2048: 22.4).  About
+// 64 on a stream of few compute units, where more blocks only queue.
 static int64_t ds_spb(const hl_handle* h, int32_t n_samples, int32_t bps, int64_t n_lookups, const void* workspace,
-                      size_t ws_bytes) {
-  // About 64 blocks: fewer leave a small mini-batch's dependent loads to a few
-  // CUs, more lengthen the look-back chain and the cold inserts' contention.
-  int64_t lpb = n_lookups / DS_BLOCKS_AIM;
-  lpb = lpb < DS_LOOKUPS_MIN ? DS_LOOKUPS_MIN : (lpb > DS_LOOKUPS_MAX ? DS_LOOKUPS_MAX : lpb);
-  int64_t spb = n_lookups > 0 ? (lpb * n_samples + n_lookups - 1) / n_lookups : DS_MAX_SPB;
-  const int64_t bag_cap = DS_MAX_BAGS / bps;
-  if (spb > bag_cap) spb = bag_cap;
-  if (spb > DS_MAX_SPB) spb = DS_MAX_SPB;
-  if (spb < 1) spb = 1;
-  const int64_t tiles = n_samples > 0 ? (n_samples + spb - 1) / spb : 0;
-  if (tiles == 0 || bps > DS_MAX_BAGS || tiles > HL_DISP_MAX_TILES || h->n_tables > DS_MAX_TABLES || !workspace ||
-      ws_bytes < HL_WS_HEADER)
+                      size_t ws_bytes, int cus) {
+  if (n_samples == 0 || bps > DS_MAX_BAGS || h->n_tables > DS_MAX_TABLES || !workspace || ws_bytes < HL_WS_HEADER)
     return 0;
-  return spb;
+  for (int64_t aim : {DS_BLOCKS_WIDE, DS_BLOCKS_AIM}) {
+    if (aim == DS_BLOCKS_WIDE && cus <= DS_BLOCKS_WIDE) continue;
+    int64_t lpb = n_lookups / aim;
+    const int64_t most = aim == DS_BLOCKS_WIDE ? 2 * DS_LOOKUPS_MAX : DS_LOOKUPS_MAX;
+    lpb = lpb < DS_LOOKUPS_MIN ? DS_LOOKUPS_MIN : (lpb > most ? most : lpb);
+    int64_t spb = n_lookups > 0 ? (lpb * n_samples + n_lookups - 1) / n_lookups : DS_MAX_SPB;
+    const int64_t bag_cap = DS_MAX_BAGS / bps;
+    if (spb > bag_cap) spb = bag_cap;
+    if (spb > DS_MAX_SPB) spb = DS_MAX_SPB;
+    if (spb < 1) spb = 1;
+    if ((n_samples + spb - 1) / spb <= HL_DISP_MAX_TILES) return spb;
+  }
+  return 0;
 }
 
 bool hl_dispatch_fused(const hl_handle* h, int32_t n_samples, int32_t bps, int64_t n_lookups, const void* workspace,
                        size_t ws_bytes) {
-  return h && bps >= 1 && n_samples >= 0 && ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes) > 0;
+  return h && bps >= 1 && n_samples >= 0 && ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes, 0) > 0;
 }
 
 extern "C" hl_status hl_dispatch(hl_handle* h, const uint32_t* rows, const int32_t* bag_ptr, int32_t n_samples,
@@ -523,7 +533,7 @@ hl_status hl_dispatch_ex(hl_handle* h, const uint32_t* rows, const int32_t* bag_
   if (n_lookups > 0 && (!rows || !gids || !codes)) return HL_ERR_INVALID_ARG;
   if ((int64_t)n_samples * bps >= (1ll << 31) || n_lookups >= (1ll << 31)) return HL_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  const int64_t spb = ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes);
+  const int64_t spb = ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes, hl_stream_cus(s));
   const int64_t tiles = spb ? (n_samples + spb - 1) / spb : 0;
   if (!spb && cf && cf->table) return HL_ERR_INVALID_ARG;  // the fused plan needs the fused dispatch
   if (!spb) {
