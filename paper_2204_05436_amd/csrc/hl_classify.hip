@@ -330,7 +330,7 @@ extern "C" hl_status hl_remap(const hl_handle* h, const uint32_t* gids, int64_t 
 #define DS_BLOCKS_AIM 64    // on streams of at most DS_BLOCKS_WIDE compute units
 #define DS_BLOCKS_WIDE 160   // on others
 #define DS_MAP 8192         // lookups per block mapped to their bag in LDS
-#define DS_TICKET 0         // 64-bit: the call's epoch over the tiles handed out
+#define DS_TICKET 0         // (hl_ticket)
 __global__ void __launch_bounds__(DS_THREADS)
 ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr, int32_t n_samples, int32_t bps,
           int32_t spb, const uint32_t* __restrict__ base, const uint32_t* __restrict__ nrow, int32_t n_tables,
@@ -347,14 +347,10 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
   hl_hook_head(hk);
   hl_hook_gate(hk);
   if (tid == 0) {
-    // one atomic hands out the tile and the call's epoch (status words of earlier
-    // calls carry older ones; zeroed words carry no flag); the block that takes
-    // the last tile resets the tiles and advances the epoch for the next call
-    unsigned long long* tk = (unsigned long long*)(hdr + DS_TICKET);
-    const unsigned long long x = atomicAdd(tk, 1ull);
-    s_tile = (uint32_t)x;
-    s_epoch = (uint32_t)(x >> 32);
-    if (s_tile == gridDim.x - 1) atomicAdd(tk, (1ull << 32) - gridDim.x);
+    // (published words of earlier calls carry older epochs; zeroed words no flag)
+    uint32_t e;
+    s_tile = hl_ticket(hdr + DS_TICKET, gridDim.x, &e);
+    s_epoch = e;
   }
   __syncthreads();
   const uint32_t tile = s_tile, epoch = s_epoch;

@@ -61,27 +61,25 @@ eb_fwd_oh(const void* w_hot, const void* stg, int32_t stg_rows, uint32_t n_hot, 
 }
 
 // The forward over every bag of a one-hot mini-batch and the backward's
-// grouping in one launch: blocks [0, T) each sort a table (the grouping's
-// second step, after gt_prep: gt_sort_body), the others pool the bags.  The
-// sort reads the prep's keys and writes the grouping, the forward reads the
-// codes and rows and writes the pooled outputs: nothing one writes is read by
-// the other, so they run side by side (the sort on a few compute units at LDS
-// and latency speed, the HBM-bound forward on the rest).
-template <int VEC, bool BF, int ITEMS>
+// grouping in one launch: the first T blocks each sort a table (gt_sort_body),
+// the others pool the bags and check that every bag is one-hot.  Nothing one side
+// writes is read by the other, so they run side by side (the sorts on a few
+// compute units at LDS and latency speed, the HBM-bound forward on the rest).
+// CODES: the sorts read the slot codes themselves, T apart, which spares the
+// launch of gt_prep (GT_CODES_E); otherwise gt_prep's keys.
+template <int VEC, bool BF, int ITEMS, bool CODES>
 __global__ void __launch_bounds__(GT_THREADS)
 eb_fwd_gt(const void* w_hot, const void* stg, int32_t stg_rows, uint32_t n_hot, uint32_t k_cap,
           const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr, float* __restrict__ out, eb_geom g,
-          int64_t n_lookups, int64_t n_bags, const uint32_t* __restrict__ keys_tm, const uint32_t* __restrict__ cum,
-          uint32_t nblk, uint32_t E, int32_t T, const uint32_t* __restrict__ tb, uint32_t* __restrict__ kout,
-          uint32_t* __restrict__ vout, uint32_t* err, int ballot_only, hl_hook hk) {
+          int64_t n_lookups, int64_t n_bags, gt_src src, uint32_t E, int32_t T, const uint32_t* __restrict__ tb,
+          uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t* err, int ballot_only, hl_hook hk) {
   __shared__ uint32_t s_code[GT_WAVES][OH_UNIT];
   hl_hook_head(hk);
   if (blockIdx.x < (uint32_t)T) {
-    gt_sort_body<ITEMS>(blockIdx.x, keys_tm, cum, nblk, E, T, (uint32_t)n_bags, tb, n_hot, kout, vout, err,
-                        ballot_only);
+    gt_sort_body<ITEMS, CODES>(blockIdx.x, src, E, T, (uint32_t)n_bags, tb, n_hot, kout, vout, err, ballot_only);
   } else {
     eb_fwd_oh_body<VEC, BF, 0>(blockIdx.x - T, gridDim.x - T, w_hot, stg, stg_rows, n_hot, k_cap, codes, bag_ptr,
-                               out, g, n_lookups, n_bags, err, s_code);
+                               out, g, n_lookups, n_bags, err, s_code, 0, INT64_MAX, true);
   }
 }
 
@@ -1072,10 +1070,17 @@ static int eb_device_cus(const hl_handle* h) {
   return cus[d];
 }
 
+// Lookups per table up to which the sorts beside the forward read the codes
+// themselves: each lane's code is a cache line of its own, which a block's
+// compute unit takes one a cycle, while the forward keeps the memory busy.
+// gt_prep and the launch, then the launch alone: 1024 per table (8 tables, rows
+// of 16) 4.2 + 10.7 us, 10.1; 4096 (26 tables, rows of 16) 5.6 + 13.1, 15.8;
+// 8192 (26 tables, rows of 64) 5.6 + 20.1, 32.7.
+#define GT_CODES_E 4096
 template <int VEC, bool BF>
 static void launch_fwd_gt(hl_handle* h, hipStream_t s, const void* w_hot, const void* stg, int32_t stg_rows,
                           const int32_t* codes, const int32_t* bag_ptr, float* out, eb_geom g, int64_t n_lookups,
-                          int64_t n_bags, const uint32_t* k_tm, const uint32_t* cum, uint32_t nblk, uint32_t* kout,
+                          int64_t n_bags, void* workspace, uint32_t* k_tm, uint32_t* cum, uint32_t* kout,
                           uint32_t* vout) {
   const int32_t T = h->n_tables;
   const uint32_t E = (uint32_t)(n_bags / T);
@@ -1084,12 +1089,27 @@ static void launch_fwd_gt(hl_handle* h, hipStream_t s, const void* w_hot, const 
   const int cus = eb_device_cus(h);
   const uint32_t nf = (uint32_t)(cus > 2 * T ? cus - T : cus);
   const hl_hook hk = hl_hook_take(h);
-#define FGT(I)                                                                                                    \
-  HL_KERNEL(h, s, "eb_fwd_gt", (eb_fwd_gt<VEC, BF, I>), dim3(T + nf), dim3(GT_THREADS), 0, s, w_hot, stg, stg_rows, \
-            h->n_hot, h->k_cap, codes, bag_ptr, out, g, n_lookups, n_bags, k_tm, cum, nblk, E, T, h->d_tb, kout,     \
-            vout, h->d_err, h->ballot_ranks, hk)
-  if (E <= 4 * GT_THREADS) FGT(4);
-  else FGT(8);
+  gt_src src{};
+  if (E <= GT_CODES_E) {
+    src.codes = codes;
+    src.k_cap = h->k_cap;
+    src.stg_rows = stg_rows;
+    src.ticket = (uint32_t*)workspace + HL_HDR_GT;
+    src.st = (uint64_t*)((uint32_t*)workspace + HL_HDR_GSTAT);
+  } else {
+    src.keys_tm = k_tm;
+    src.cum = cum;
+    src.nblk = hl_group_prep(h, const_cast<int32_t*>(codes), bag_ptr, n_bags, stg_rows, k_tm, cum, nullptr, 0, nullptr, s);
+  }
+#define FGT(I, C)                                                                                                 \
+  HL_KERNEL(h, s, "eb_fwd_gt", (eb_fwd_gt<VEC, BF, I, C>), dim3(T + nf), dim3(GT_THREADS), 0, s, w_hot, stg, stg_rows, \
+            h->n_hot, h->k_cap, codes, bag_ptr, out, g, n_lookups, n_bags, src, E, T, h->d_tb, kout, vout, h->d_err, \
+            h->ballot_ranks, hk)
+  static_assert(GT_CODES_E == 4 * GT_THREADS, "items per thread");
+  if (E <= GT_THREADS) FGT(1, true);
+  else if (E <= 2 * GT_THREADS) FGT(2, true);
+  else if (E <= 4 * GT_THREADS) FGT(4, true);
+  else FGT(8, false);
 #undef FGT
 }
 
@@ -1148,10 +1168,8 @@ extern "C" hl_status hl_embbag_fwd_plan(hl_handle* h, const void* w_hot, const v
   hl_sort_result(ws.sort, bw_key_bits(h, stg_rows), &rk, &rv);
   uint32_t* tk = rk == ws.sort.k0 ? ws.sort.k1 : ws.sort.k0;
   uint32_t* tv = rv == ws.sort.v0 ? ws.sort.v1 : ws.sort.v0;
-  const uint32_t nblk = hl_group_prep(h, const_cast<int32_t*>(codes), bag_ptr, n_bags, stg_rows, tk, tv, nullptr, 0,
-                                      nullptr, s);
-#define FG(V, B) launch_fwd_gt<V, B>(h, s, w_hot, staging, stg_rows, codes, bag_ptr, out, g, n_lookups, n_bags, tk, tv, \
-                                     nblk, rk, rv)
+#define FG(V, B) launch_fwd_gt<V, B>(h, s, w_hot, staging, stg_rows, codes, bag_ptr, out, g, n_lookups, n_bags, workspace, \
+                                     tk, tv, rk, rv)
   if (bf) FG(4, true);
   else FG(4, false);
 #undef FG

@@ -562,7 +562,8 @@ static inline int64_t eb_oh_units(const eb_geom& g, int vec, int64_t n_bags) {
 }
 
 // The work of block bid of nblk (each of blockDim.x / 64 waves) on the units
-// [u0, u1); s_code: a row of OH_UNIT words in LDS per wave.
+// [u0, u1); s_code: a row of OH_UNIT words in LDS per wave.  strict: a bag that
+// is not one-hot is also an error of the call (HL_DEVERR_SHAPE).
 template <int VEC, bool BF, int PART>
 __device__ __forceinline__ void eb_fwd_oh_body(uint32_t bid, uint32_t nblk, const void* w_hot_, const void* stg_,
                                                int32_t stg_rows, uint32_t n_hot, uint32_t k_cap,
@@ -570,7 +571,7 @@ __device__ __forceinline__ void eb_fwd_oh_body(uint32_t bid, uint32_t nblk, cons
                                                const int32_t* __restrict__ bag_ptr, float* __restrict__ out,
                                                eb_geom g, int64_t n_lookups, int64_t n_bags, uint32_t* err,
                                                uint32_t (*s_code)[OH_UNIT], int64_t u0 = 0,
-                                               int64_t u1 = INT64_MAX) {
+                                               int64_t u1 = INT64_MAX, bool strict = false) {
   static_assert(PART == 0 || PART == 1, "whole forward or its hot half");
   typedef typename RowIO<VEC, BF>::T T;
   const T* w_hot = (const T*)w_hot_;
@@ -607,6 +608,7 @@ __device__ __forceinline__ void eb_fwd_oh_body(uint32_t bid, uint32_t nblk, cons
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (__ballot(bad)) {
+      if (strict && lane == 0) hl_flag(err, HL_DEVERR_SHAPE);
       // some bag of the unit is not one-hot: bag by bag, its hot rows then
       // (PART 0) its staging rows, in CSR order
       if (gact)

@@ -129,7 +129,11 @@ gt_sort(const uint32_t* __restrict__ keys_tm, const uint32_t* __restrict__ cum, 
         int32_t T, uint32_t n, const uint32_t* __restrict__ tb, uint32_t n_hot, uint32_t* __restrict__ kout,
         uint32_t* __restrict__ vout, uint32_t* err, int ballot_only, hl_hook hk) {
   hl_hook_head(hk);  // a handover signal: the codes are complete (gt_prep has ended)
-  gt_sort_body<ITEMS>(blockIdx.x, keys_tm, cum, nblk, E, T, n, tb, n_hot, kout, vout, err, ballot_only);
+  gt_src src{};
+  src.keys_tm = keys_tm;
+  src.cum = cum;
+  src.nblk = nblk;
+  gt_sort_body<ITEMS, false>(blockIdx.x, src, E, T, n, tb, n_hot, kout, vout, err, ballot_only);
 }
 
 // ----------------------------------------------------------------------------- host
@@ -162,7 +166,9 @@ hl_status hl_group_by_table(hl_handle* h, int32_t* codes, const int32_t* bag_ptr
 #define GTS(I)                                                                                                    \
   HL_KERNEL(h, s, "gt_sort", gt_sort<I>, dim3(T), dim3(GT_THREADS), 0, s, k_tm, cum, nblk, E, T, (uint32_t)n_bags, \
             h->d_tb, h->n_hot, kout, vout, h->d_err, h->ballot_ranks, hk)
-  if (E <= 4 * GT_THREADS) GTS(4);
+  if (E <= GT_THREADS) GTS(1);
+  else if (E <= 2 * GT_THREADS) GTS(2);
+  else if (E <= 4 * GT_THREADS) GTS(4);
   else GTS(8);
 #undef GTS
   HL_LAUNCHED();

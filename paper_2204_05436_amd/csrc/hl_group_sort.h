@@ -36,11 +36,24 @@ __device__ __forceinline__ uint32_t gt_scan(uint32_t v, uint32_t* ws, uint32_t* 
   return x - v + off;
 }
 
-// Sorts table t (a block of GT_THREADS threads).
-template <int ITEMS>
-__device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restrict__ keys_tm,
-                                             const uint32_t* __restrict__ cum, uint32_t nblk, uint32_t E, int32_t T,
-                                             uint32_t n, const uint32_t* __restrict__ tb, uint32_t n_hot,
+// Where a table's sort takes its keys: from gt_prep (table-major keys, and per
+// prep block the hot keys of the tables before each), or (codes not NULL) from
+// the slot codes themselves, with the hot keys of the earlier tables published
+// by their blocks (the table by ticket, so those are running).
+struct gt_src {
+  const uint32_t *keys_tm, *cum;
+  uint32_t nblk;
+  const int32_t* codes;
+  uint32_t k_cap;
+  int32_t stg_rows;
+  uint32_t* ticket;  // header words: hl_ticket, and the published words
+  uint64_t* st;
+};
+
+// Sorts a table (a block of GT_THREADS threads): table tb_index, or by ticket.
+template <int ITEMS, bool CODES>
+__device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& src, uint32_t E, int32_t T, uint32_t n,
+                                             const uint32_t* __restrict__ tb, uint32_t n_hot,
                                              uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t* err,
                                              int ballot_only) {
   // a sorted item in LDS: compressed key in the high word, table-major
@@ -49,8 +62,28 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
   __shared__ uint32_t wcnt[GT_WAVES][GT_NB];
   __shared__ uint32_t dofs[GT_NB];
   __shared__ uint32_t scan_ws[GT_WAVES];
-  __shared__ uint32_t s_max, s_sent, s_hb, s_ht;
+  __shared__ uint32_t s_max, s_sent, s_hb, s_ht, s_table, s_epoch;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t t = tb_index, epoch = 0;
+  if constexpr (CODES) {
+    if (tid == 0) {
+      uint32_t e;
+      s_table = hl_ticket(src.ticket, (uint32_t)T, &e);
+      s_epoch = e;
+    }
+    __syncthreads();
+    t = s_table;
+    epoch = s_epoch;
+  }
+  const uint32_t* __restrict__ keys_tm = src.keys_tm;
+  const uint32_t* __restrict__ cum = src.cum;
+  const uint32_t nblk = CODES ? 0u : src.nblk;
+  // position ps of the table: lookup ps T + t
+  auto load = [&](uint32_t ps) -> uint32_t {
+    const uint32_t q = min(ps, E - 1);
+    if constexpr (CODES) return (uint32_t)src.codes[(uint64_t)q * (uint32_t)T + t];
+    else return keys_tm[(uint64_t)t * E + q];
+  };
   const uint32_t lo = tb[t], R = tb[t + 1] - lo;  // the table's hot slots
   // the table's keys, position w * 64 ITEMS + 64 k + lane (lookup order), and
   // the hot keys of the earlier tables (hb) and up to this one (ht) summed
@@ -59,7 +92,7 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
     const uint32_t ps = (uint32_t)w * (ITEMS * 64) + k * 64 + lane;
-    key[k] = keys_tm[(uint64_t)t * E + min(ps, E - 1)];
+    key[k] = load(ps);
     pos[k] = ps;
   }
   uint32_t hb = 0, ht = 0;
@@ -82,7 +115,7 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
 #pragma unroll
       for (int k = 0; k < ITEMS; ++k) {
         const uint32_t ps = (uint32_t)w * (ITEMS * 64) + k * 64 + lane;
-        key[k] = keys_tm[(uint64_t)t * E + min(ps, E - 1)];
+        key[k] = load(ps);
         pos[k] = ps;
       }
     }
@@ -90,15 +123,24 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
     // code, or a hot slot of another table's row) one past the largest
     uint32_t kmax = 0;
     bool foreign = false, anysent = false;
+    uint32_t nhot = 0;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
       const uint32_t ps = (uint32_t)w * (ITEMS * 64) + k * 64 + lane;
       const bool valid = ps < E;
-      const uint32_t kk = key[k];
+      uint32_t kk = key[k];
+      if constexpr (CODES) {
+        kk = bw_key(kk, n_hot, src.k_cap, src.stg_rows);
+        if (valid && kk == EB_SENT) foreign = true;  // (a code that names no row)
+      }
       uint32_t c = EB_SENT;
       if (kk < n_hot) {
-        if (kk - lo < R) c = kk - lo;
-        else foreign = true;
+        if (kk - lo < R) {
+          c = kk - lo;
+          if (CODES && valid) ++nhot;
+        } else {
+          foreign = true;
+        }
       } else if (kk != EB_SENT) {
         c = R + (kk - n_hot);
       }
@@ -111,7 +153,13 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
     for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor(kmax, o));
     if (lane == 0) atomicMax(&s_max, kmax);
     if (anysent) s_sent = 1;
-    if (fresh) {
+    if constexpr (CODES) {
+      if (fresh) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) nhot += __shfl_xor(nhot, o);
+        if (lane == 0) atomicAdd(&s_ht, nhot);
+      }
+    } else if (fresh) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) {
         hb += __shfl_xor(hb, o);
@@ -123,6 +171,7 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
       }
     }
     __syncthreads();
+    if (CODES && fresh && tid == 0) hl_st_store(src.st + t, hl_st_pack(epoch, HL_ST_AGG, s_ht));
     const uint32_t sent = max(s_max + 1, R);  // after every valid key, never below R (not hot)
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k)
@@ -229,7 +278,8 @@ __device__ __forceinline__ void gt_sort_body(uint32_t t, const uint32_t* __restr
   }
   // hot pairs of this table (keys below R, sorted first): h of them, after
   // the earlier tables' H; the others before the earlier tables' E t - H
-  const uint32_t H = s_hb, h = s_ht - s_hb;
+  uint32_t H = s_hb, h = s_ht - s_hb;
+  if constexpr (CODES) H = hl_block_before(src.st, t, epoch, err);
   const uint64_t nb0 = (uint64_t)n - ((uint64_t)E * t - H) - (E - h);
   const uint32_t sent_key = max(s_max + 1, R);
 #pragma unroll

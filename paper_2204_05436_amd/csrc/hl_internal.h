@@ -192,8 +192,10 @@ __device__ __forceinline__ int32_t hl_hot_slot(const uint64_t* __restrict__ bm,
 #define HL_WS_HEADER 16384
 #define HL_HDR_SORT 0    // 8 words: per-pass tile counters
 #define HL_HDR_COLD 16   // 16 words: cold-gather counters
-#define HL_HDR_DISP 64   // 8 words: dispatch epoch, done counter, tile counter
-#define HL_HDR_DSTAT 128 // dispatch look-back status words (64-bit), to the header's end
+#define HL_HDR_DISP 64   // 2 words: dispatch ticket
+#define HL_HDR_GT 72     // 2 words: ticket of the tables' sorts beside the forward
+#define HL_HDR_GSTAT 128 // 64 published words (64-bit) of theirs
+#define HL_HDR_DSTAT 256 // dispatch's published words (64-bit), to the header's end
 #define HL_DISP_MAX_TILES ((HL_WS_HEADER - 4 * HL_HDR_DSTAT) / 8)
 // Workspace carving with 256-byte alignment.
 struct hl_carver {
@@ -493,6 +495,18 @@ __device__ __forceinline__ void hl_st_store(uint64_t* p, uint64_t w) {
 __device__ __forceinline__ uint64_t hl_st_load(const uint64_t* p) {
   return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A ticket of a launch of `n` takers and the call's epoch, in one 64-bit word
+// (epoch over the tickets handed out, in the workspace header): the taker of the
+// last ticket resets the tickets and advances the epoch for the next call, so
+// published words tagged with the epoch need no clearing between calls.
+__device__ __forceinline__ uint32_t hl_ticket(uint32_t* word, uint32_t n, uint32_t* epoch) {
+  unsigned long long* tk = (unsigned long long*)word;
+  const unsigned long long x = atomicAdd(tk, 1ull);
+  if ((uint32_t)x == n - 1) atomicAdd(tk, (1ull << 32) - n);
+  *epoch = (uint32_t)(x >> 32);
+  return (uint32_t)x;
+}
+
 // Exclusive prefix of `tile` over tiles [0, tile) from single-value status
 // words (hl_st_pack), read by the whole block: thread t looks at tile j - t of
 // the current window, so one round trip covers blockDim.x predecessors, and the

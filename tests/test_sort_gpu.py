@@ -66,3 +66,44 @@ def test_grouping_sort(n, layout, bits):
         assert hl.hl_last_device_error(h) == 0
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 64), (333, 64), (1023, 3), (1024, 2), (1025, 3), (2048, 2), (2049, 2),
+                                 (4096, 2), (4097, 2), (8191, 1)])
+def test_forward_with_table_sorts(B, T):
+    """The forward with the tables' sorts in its launch (hl_embbag_fwd_plan) at
+    the edges of its items per thread and of where the sorts read the codes
+    themselves: every pooled row, the grouping, and a mini-batch of as many
+    lookups as bags that is not one-hot (HL_DEVERR_SHAPE); called several times,
+    since the tables' published counts are told apart by an epoch."""
+    rng = np.random.default_rng(B * 100 + T)
+    dim, per, n = 8, 50, B * T
+    h = hl.hl_create(np.full(T, per, np.uint32), dim, "f32", per * T)
+    try:
+        hot = np.sort(rng.permutation(per * T)[:max(1, per * T // 3)]).astype(np.int32)
+        n_hot, k_cap, n_stg = hot.size, per * T, per * T
+        hl.hl_set_hot(h, torch.from_numpy(hot).cuda(), n_hot)
+        ptr = np.arange(n + 1, dtype=np.int32)
+        dp = torch.from_numpy(ptr).cuda()
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, n, B), dtype=torch.uint8, device="cuda")
+        w = torch.randn((n_hot + n_stg, dim), device="cuda")
+        out = torch.zeros((n, dim), device="cuda")
+        keys, bags = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+        for again in range(3):
+            gid = (rng.zipf(1.3, n) % per) + per * (np.arange(n) % T)
+            at = np.minimum(np.searchsorted(hot, gid), n_hot - 1)
+            codes = np.where(hot[at] == gid, at, k_cap + gid).astype(np.int32)
+            dc = torch.from_numpy(codes).cuda()
+            hl.hl_embbag_fwd_plan(h, w[:n_hot], w[n_hot:], n_stg, dc, dp, B, T, n, out, ws)
+            hl.hl_embbag_bwd_grouping(h, n_stg, B, T, n, ws, keys, bags)
+            row = np.where(codes < n_hot, codes, n_hot + codes - k_cap)
+            assert torch.equal(out, w[torch.from_numpy(row).cuda()])
+            check_grouping(keys.cpu().numpy().view(np.uint32), bags.cpu().numpy().view(np.uint32), codes,
+                           np.arange(n, dtype=np.uint32), n_hot, k_cap, f"{B}x{T}")
+            assert hl.hl_last_device_error(h) == 0
+        if -(-B // 32) * (T + 1) <= n:  # (else: the general sort, which takes any bags)
+            ptr[1] = 2  # the first bag holds two lookups, the second none
+            hl.hl_embbag_fwd_plan(h, w[:n_hot], w[n_hot:], n_stg, dc, torch.from_numpy(ptr).cuda(), B, T, n, out, ws)
+            assert hl.hl_last_device_error(h) & hl.DEVERR["SHAPE"]
+    finally:
+        h.close()
