@@ -420,6 +420,8 @@ struct hl_sort_src {
   uint32_t* sflag;
   uint32_t sv;
   hl_cg_fused cf;
+  const uint32_t* ids;   // not NULL: pairs (hl_set_of(id, n_sets), id) of these, which srt_count forms
+  uint32_t n_sets;
 };
 // The forward over every sample, run in the launches of a sort's passes by the
 // blocks past the sort's own (hl_fwd_sort.h; hl_fwd_sort_side gives `passes` for
@@ -437,6 +439,20 @@ typedef decltype(hl_sort_side::passes) hl_sort_side_fn;
 hl_sort_side_fn hl_fwd_sort_side(bool bf16, int vec);
 hl_status hl_sort_codes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int bits, hipStream_t s,
                         uint32_t** out_k, uint32_t** out_v, const hl_sort_side* side = nullptr);
+// Sorts (hl_set_of(id, n_sets), id) of n ids by set.
+hl_status hl_sort_ids_by_set(hl_handle* h, hl_sort_ws& ws, const uint32_t* ids, uint32_t n_sets, uint32_t n,
+                             hipStream_t s, uint32_t** out_k, uint32_t** out_v);
+// The set of an id in the access logger (MurmurHash3's 32-bit finalizer); an
+// invalid id (0xFFFFFFFF) gets n_sets, which sorts after every set.
+__device__ __forceinline__ uint32_t hl_set_of(uint32_t g, uint32_t n_sets) {
+  uint32_t x = g;
+  x ^= x >> 16;
+  x *= 0x85EBCA6Bu;
+  x ^= x >> 13;
+  x *= 0xC2B2AE35u;
+  x ^= x >> 16;
+  return g == 0xFFFFFFFFu ? n_sets : x % n_sets;
+}
 // Compute units in a stream's mask (0 if it cannot be read).
 int hl_stream_cus(hipStream_t s);
 

@@ -1,5 +1,6 @@
-// Stable LSD radix sort of (key, value) uint32 pairs, or of the backward's
-// (key, bag) pairs read from the slot codes.
+// Stable LSD radix sort of (key, value) uint32 pairs, of the backward's (key,
+// bag) pairs read from the slot codes, or of the access logger's (set, id) pairs
+// read from the ids.
 //
 // A sort of `bits` bits takes P = ceil(bits / 11) passes of b = ceil(bits / P)
 // bits (two passes of 10 bits for 20-bit keys), in P + 1 launches over the same
@@ -7,7 +8,8 @@
 //
 //   srt_count -- each tile's digit counts of every pass in one read of the keys
 //                (from slot codes: it forms them, points the fused plan's cold
-//                codes at their staging rows, and nothing is written per item).
+//                codes at their staging rows, and nothing is written per item;
+//                from ids: it forms and writes the pairs).
 //   srt_pass  -- one per digit.  A block ranks its tile's items by digit with
 //                per-wave LDS counters that the lanes of one digit advance
 //                together (their peer mask found by ballots), reorders the tile
@@ -72,7 +74,7 @@ __global__ void __launch_bounds__(HL_SORT_THREADS)
 srt_count(hl_sort_src src, const uint32_t* n_dev, uint32_t n_host, int passes, int b, uint32_t tile,
           uint32_t* __restrict__ row0, uint32_t* __restrict__ row1, uint32_t* __restrict__ row2,
           uint32_t* __restrict__ row3, uint64_t* __restrict__ grp0, uint64_t* __restrict__ grp1,
-          uint64_t* __restrict__ gtot, uint32_t* err) {
+          uint64_t* __restrict__ gtot, uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t* err) {
   __shared__ uint32_t h[HL_SORT_MAXPASS][NB];
   bw_start_signal(src.sflag, src.sv);
   const uint32_t n = srt_n(n_dev, n_host);
@@ -97,7 +99,7 @@ srt_count(hl_sort_src src, const uint32_t* n_dev, uint32_t n_host, int passes, i
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t i = i0 + u * HL_SORT_THREADS;
-      k[u] = i < te ? (src.codes ? (uint32_t)src.codes[i] : src.k[i]) : 0u;
+      k[u] = i < te ? (src.codes ? (uint32_t)src.codes[i] : (src.ids ? src.ids[i] : src.k[i])) : 0u;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -117,6 +119,10 @@ srt_count(hl_sort_src src, const uint32_t* n_dev, uint32_t n_host, int passes, i
           key = bw_key(key, src.n_hot, src.k_cap, src.stg_rows);
           bad = bad || key == EB_SENT;
         }
+      } else if (src.ids) {
+        vout[i] = key;
+        key = hl_set_of(key, src.n_sets);
+        kout[i] = key;
       }
       for (int p = 0; p < passes; ++p) atomicAdd(&h[p][(key >> (b * p)) & mask], 1u);
     }
@@ -185,7 +191,7 @@ static hl_status srt_run(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, c
   const uint32_t tile = (uint32_t)(HL_SORT_THREADS * items), tiles = hl_div_up(n_host, tile);
 #define CNT(NB)                                                                                                      \
   HL_KERNEL(h, s, "srt_count", srt_count<NB>, dim3(tiles), dim3(HL_SORT_THREADS), 0, s, src, n_dev, n_host, pl.passes, \
-            pl.b, tile, ws.row[0], ws.row[1], ws.row[2], ws.row[3], ws.grp[0], ws.grp[1], ws.gtot, h->d_err)
+            pl.b, tile, ws.row[0], ws.row[1], ws.row[2], ws.row[3], ws.grp[0], ws.grp[1], ws.gtot, ws.k0, ws.v0, h->d_err)
   if (pl.nb == 256) CNT(256);
   else if (pl.nb == 512) CNT(512);
   else if (pl.nb == 1024) CNT(1024);
@@ -212,6 +218,14 @@ hl_status hl_sort_pairs(hl_handle* h, hl_sort_ws& ws, const uint32_t* n_dev, uin
   hl_sort_src src{};
   src.k = ws.k0;
   return srt_run(h, ws, src, n_dev, n_host, bits, s, out_k, out_v, nullptr);
+}
+
+hl_status hl_sort_ids_by_set(hl_handle* h, hl_sort_ws& ws, const uint32_t* ids, uint32_t n_sets, uint32_t n,
+                             hipStream_t s, uint32_t** out_k, uint32_t** out_v) {
+  hl_sort_src src{};
+  src.ids = ids;
+  src.n_sets = n_sets;
+  return srt_run(h, ws, src, nullptr, n, hl_bit_width(n_sets), s, out_k, out_v, nullptr);
 }
 
 hl_status hl_sort_codes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int bits, hipStream_t s,

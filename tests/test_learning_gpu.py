@@ -72,7 +72,7 @@ def test_count_and_topk(n_rows, tables):
                                            (1, 16, 137), (3, 16, 5000), (7, 3, 9000), (40, 16, 20011), (300, 2, 3000)])
 def test_logger_long_runs(n_sets, ways, n):
     """The access logger's replay of runs around the lengths where it changes
-    form (8 accesses by one thread, then 64 at a time by a wave): few sets, so
+    form (8 accesses by 16 lanes, then 64 at a time by a wave): few sets, so
     that every batch gives each a long run; ids from all hits to all misses;
     every entry against the oracle after each batch."""
     rng = np.random.default_rng(n * 31 + ways)
