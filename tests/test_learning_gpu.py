@@ -69,7 +69,8 @@ def test_count_and_topk(n_rows, tables):
 
 
 @pytest.mark.parametrize("n_sets,ways,n", [(1, 16, 7), (1, 16, 8), (1, 5, 9), (1, 16, 71), (2, 1, 81), (1, 16, 72),
-                                           (1, 16, 137), (3, 16, 5000), (7, 3, 9000), (40, 16, 20011), (300, 2, 3000)])
+                                           (1, 16, 137), (3, 16, 5000), (7, 3, 9000), (40, 16, 20011), (300, 2, 3000),
+                                           (1, 16, 328), (1, 16, 336), (1, 7, 700)])
 def test_logger_long_runs(n_sets, ways, n):
     """The access logger's replay of runs around the lengths where it changes
     form (8 accesses by 16 lanes, then 64 at a time by a wave): few sets, so
