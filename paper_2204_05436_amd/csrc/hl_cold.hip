@@ -20,6 +20,8 @@
 // list and count, so it can run on a stream of its own while the popular
 // mu-batch and the backward's grouping proceed (the overlap of the paper's
 // pipeline, Sec. IV and Fig. "hotlinepipe").
+#include <algorithm>
+
 #include "hl_internal.h"
 
 #define CG_C_NCOLD 1
@@ -99,32 +101,33 @@ template <typename F>
 __device__ __forceinline__ void cg_lookups(const cg_sel& sel, const int32_t* __restrict__ bag_ptr,
                                            const int32_t* codes, const uint32_t* gids, uint32_t n_lookups, uint32_t* err,
                                            F f) {
-  const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-  int64_t b0 = 0, b1 = sel.sel_bags;
-  if (sel.ids) {
-    const int32_t q = (int32_t)(t / (uint32_t)sel.tps);
-    const int32_t n = sel.n_dev ? min(max(*sel.n_dev, 0), sel.n_max) : sel.n_max;
-    if (q >= n) return;
+  auto end = [&](int64_t bag) { return (uint32_t)min(max((int64_t)bag_ptr[bag], (int64_t)0), (int64_t)n_lookups); };
+  if (!sel.ids) {
+    const uint32_t t = blockIdx.x * 256 + threadIdx.x, lo = end(0), hi = end(sel.sel_bags);
+    if (t < n_lookups) {
+      const int32_t c = codes[t];
+      const uint32_t g = gids ? gids[t] : 0u;
+      if (c == -1 && t >= lo && t < hi) f(t, g);
+    }
+    return;
+  }
+  // (the grid covers a list of every sample; a longer one, which names samples
+  // again, in turns: n_max is only a bound and may be any number)
+  const uint32_t tps = (uint32_t)sel.tps, per = 256 / tps, r = threadIdx.x % tps;
+  const int64_t n = sel.n_dev ? min(max(*sel.n_dev, 0), sel.n_max) : sel.n_max;
+  for (int64_t q = (int64_t)blockIdx.x * per + threadIdx.x / tps; q < n; q += (int64_t)gridDim.x * per) {
     const int32_t s = sel.ids[q];
     if (s < 0 || s >= sel.n_samples) {
-      if (t % (uint32_t)sel.tps == 0) hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
-      return;
+      if (r == 0) hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+      continue;
     }
-    b0 = (int64_t)s * sel.bps;
-    b1 = b0 + sel.bps;
-  }
-  const uint32_t lo = (uint32_t)min(max((int64_t)bag_ptr[b0], (int64_t)0), (int64_t)n_lookups);
-  const uint32_t hi = (uint32_t)min(max((int64_t)bag_ptr[b1], (int64_t)0), (int64_t)n_lookups);
-  if (sel.ids) {
-    for (uint32_t i = lo + t % (uint32_t)sel.tps; i < hi; i += (uint32_t)sel.tps) {
+    const int64_t b0 = (int64_t)s * sel.bps;
+    const uint32_t hi = end(b0 + sel.bps);
+    for (uint32_t i = end(b0) + r; i < hi; i += tps) {
       const int32_t c = codes[i];
       const uint32_t g = gids ? gids[i] : 0u;
       if (c == -1) f(i, g);
     }
-  } else if (t < n_lookups) {
-    const int32_t c = codes[t];
-    const uint32_t g = gids ? gids[t] : 0u;
-    if (c == -1 && t >= lo && t < hi) f(t, g);
   }
 }
 
@@ -343,11 +346,14 @@ extern "C" hl_status hl_cold_plan(hl_handle* h, const uint32_t* gids, int32_t* c
   const uint32_t n = (uint32_t)n_lookups;
   // selection: the first n_sel_max samples (no list) or the listed ones; an
   // empty selection inserts nothing
-  // (a sample of more than 64 lookups or so: a block's threads, else a wave's)
+  // (a sample of about 100 lookups or more: a block's threads, else a wave's)
   const int32_t tps = n_lookups > 96ll * n_samples ? 256 : 64;
   const cg_sel sel{sample_ids, n_sel_dev, n_sel_max, n_samples, bps, tps, (int64_t)n_sel_max * bps};
   uint32_t ib = 0;
-  if (n > 0 && n_sel_max > 0) ib = sample_ids ? hl_div_up((uint64_t)n_sel_max * tps, 256) : hl_div_up(n, 256);
+  if (n > 0 && n_sel_max > 0) {
+    const uint64_t listed = std::min(n_sel_max, std::max(n_samples, 1));  // (a longer list: cg_lookups)
+    ib = sample_ids ? std::min(hl_div_up(listed * tps, 256), 1u << 20) : hl_div_up(n, 256);
+  }
   if (ib > 0)
     HL_KERNEL(h, s, "cg_insert", cg_insert, dim3(ib), dim3(256), 0, s, gids, codes, bag_ptr, sel, n, h->n_rows, table, ws,
               h->d_err);

@@ -57,3 +57,40 @@ def test_cold_plan_selection(B, bps, mean, how):
         assert hl.hl_last_device_error(h) == 0
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("n_max", [200, 1 << 26, 2**31 - 1])
+@pytest.mark.parametrize("mean", [1, 120])
+def test_cold_plan_loose_bound(n_max, mean):
+    """A list counted on the device, under bounds far above the number of samples
+    (n_sel_max only limits the count), shorter and (samples named again) longer
+    than the samples; a listed id that is no sample is reported."""
+    rng = np.random.default_rng(mean)
+    B, bps, n_rows, k_cap = 37, 3, 5000, 900
+    lens = rng.poisson(mean, B * bps)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(ptr[-1])
+    hot = np.sort(rng.permutation(n_rows)[:k_cap]).astype(np.uint32)
+    gids = (rng.zipf(1.2, n) % n_rows).astype(np.uint32)
+    codes = O.remap(hot, gids).astype(np.int32)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int32)).cuda()
+    h = hl.hl_create(np.array([n_rows], np.uint32), 4, "f32", k_cap)
+    try:
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, B * bps, B), dtype=torch.uint8, device="cuda")
+        cold, nc = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        for listed in (5, B, 190):
+            sel = np.resize(rng.permutation(B), listed).astype(np.int32)
+            cnt = torch.tensor([listed], dtype=torch.int32, device="cuda")
+            uniq = np.unique(sel).astype(np.int32)
+            want_cold, want_codes = O.cold_plan(gids, codes.copy(), ptr, uniq, uniq.size, bps, k_cap)
+            dc = d(codes)
+            hl.hl_cold_plan(h, d(gids), dc, d(ptr), B, bps, n, d(sel), cnt, n_max, n, cold, nc, ws)
+            assert int(nc.item()) == want_cold.size
+            assert np.array_equal(u32(cold[:want_cold.size]), want_cold)
+            assert np.array_equal(dc.cpu().numpy(), want_codes)
+            assert hl.hl_last_device_error(h) == 0
+        sel[189] = B
+        hl.hl_cold_plan(h, d(gids), d(codes), d(ptr), B, bps, n, d(sel), cnt, n_max, n, cold, nc, ws)
+        assert hl.hl_last_device_error(h) == hl.DEVERR["OUT_OF_RANGE"]
+    finally:
+        h.close()
