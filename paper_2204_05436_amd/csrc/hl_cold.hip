@@ -83,14 +83,21 @@ static hl_status cg_table(hl_handle* h, uint32_t S, hipStream_t s, uint64_t** ou
 }
 
 // The selected lookups: of the first sel_bags bags (ids NULL), one per thread of
-// a flat grid, or of the listed samples, tps threads (64 or 256) per sample.
+// a flat grid, or of the listed samples, tps threads (8 to 256, about as many as a
+// sample has lookups) per sample; a sample of more than CG_LONG tps lookups by the
+// whole block, four per thread at a time, and by gridDim.y blocks where samples
+// are that long on average (then its lookups are its blocks' share and more).
 // f(i, g) takes a lookup with code -1 and, when `gids` is given, its id.  One
 // lookup per thread keeps each thread to one chain of dependent accesses (probe,
 // slot, code): four per thread took 7.6 and 5.3 us (insert, codes; 212,992
 // lookups) against 4.6 and 3.3, and blocks that first compacted their cold lookups
 // in LDS 5.7 and 4.0.  A list marked in a mask over the samples by two launches of
 // its own and searched by bag: 16.7 us for the insert of 328,000 lookups in bags
-// of 20, 5.6 by the listed samples.
+// of 20, 5.6 by the listed samples.  Long samples by a sample's own threads alone,
+// one lookup at a time (whole calls, a fifth of the lookups cold): one of 320,000
+// lookups 2184 us against 283, 4 of 80,000 529 against 283, one of 40,000 among
+// 2047 of 40 923 against 309.
+#define CG_LONG 4
 struct cg_sel {
   const int32_t* ids;     // the listed samples (NULL: every sample up to sel_bags / bps)
   const int32_t* n_dev;   // their number on the device (NULL: n_max)
@@ -113,21 +120,52 @@ __device__ __forceinline__ void cg_lookups(const cg_sel& sel, const int32_t* __r
   }
   // (the grid covers a list of every sample; a longer one, which names samples
   // again, in turns: n_max is only a bound and may be any number)
+  __shared__ uint32_t l_lo[32], l_hi[32], l_n;
   const uint32_t tps = (uint32_t)sel.tps, per = 256 / tps, r = threadIdx.x % tps;
   const int64_t n = sel.n_dev ? min(max(*sel.n_dev, 0), sel.n_max) : sel.n_max;
-  for (int64_t q = (int64_t)blockIdx.x * per + threadIdx.x / tps; q < n; q += (int64_t)gridDim.x * per) {
-    const int32_t s = sel.ids[q];
-    if (s < 0 || s >= sel.n_samples) {
-      if (r == 0) hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
-      continue;
+  for (int64_t q0 = (int64_t)blockIdx.x * per; q0 < n; q0 += (int64_t)gridDim.x * per) {
+    const int64_t q = q0 + threadIdx.x / tps;
+    uint32_t lo = 0, hi = 0;
+    if (q < n) {
+      const int32_t s = sel.ids[q];
+      if (s >= 0 && s < sel.n_samples) {
+        const int64_t b0 = (int64_t)s * sel.bps;
+        lo = end(b0);
+        hi = end(b0 + sel.bps);
+      } else if (r == 0) {
+        hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
+      }
     }
-    const int64_t b0 = (int64_t)s * sel.bps;
-    const uint32_t hi = end(b0 + sel.bps);
-    for (uint32_t i = end(b0) + r; i < hi; i += tps) {
-      const int32_t c = codes[i];
-      const uint32_t g = gids ? gids[i] : 0u;
-      if (c == -1) f(i, g);
+    const bool lng = hi > lo && hi - lo > CG_LONG * tps;
+    if (!lng && blockIdx.y == 0)
+      for (uint32_t i = lo + r; i < hi; i += tps) {
+        const int32_t c = codes[i];
+        const uint32_t g = gids ? gids[i] : 0u;
+        if (c == -1) f(i, g);
+      }
+    if (threadIdx.x == 0) l_n = 0;
+    if (!__syncthreads_or(lng)) continue;
+    if (lng && r == 0) {
+      const uint32_t k = atomicAdd(&l_n, 1u);
+      l_lo[k] = lo;
+      l_hi[k] = hi;
     }
+    __syncthreads();
+    for (uint32_t k = 0; k < l_n; ++k)
+      for (uint32_t i0 = l_lo[k] + blockIdx.y * 1024 + threadIdx.x; i0 < l_hi[k]; i0 += gridDim.y * 1024) {
+        int32_t c[4];
+        uint32_t g[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t i = i0 + u * 256;
+          c[u] = i < l_hi[k] ? codes[i] : 0;
+          g[u] = gids && i < l_hi[k] ? gids[i] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (c[u] == -1) f(i0 + u * 256, g[u]);
+      }
+    __syncthreads();  // (the list is reused)
   }
 }
 
@@ -135,7 +173,8 @@ __global__ void __launch_bounds__(256)
 cg_insert(const uint32_t* __restrict__ gids, const int32_t* __restrict__ codes, const int32_t* __restrict__ bag_ptr,
           cg_sel sel, uint32_t n_lookups, uint64_t n_rows, uint64_t* table, cg_ws ws, uint32_t* err) {
   // the rank scan's status words, cleared for the kernel that follows
-  for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j < ws.rtiles; j += gridDim.x * 256) ws.rstat[j] = 0;
+  if (blockIdx.y == 0)
+    for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j < ws.rtiles; j += gridDim.x * 256) ws.rstat[j] = 0;
   cg_lookups(sel, bag_ptr, codes, gids, n_lookups, err, [&](uint32_t i, uint32_t g) {
     if (g >= n_rows) {
       hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
@@ -243,8 +282,9 @@ cg_codes(const int32_t* __restrict__ bag_ptr, cg_sel sel, uint32_t n_lookups, ui
     table[sl] = 0;
   });
   if (!fits) return;
-  const uint32_t gs = gridDim.x * blockDim.x;
-  for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < ncold; u += gs) cold_ids[u] = ws.fst[u];
+  const uint32_t gs = gridDim.x * gridDim.y * blockDim.x;
+  for (uint32_t u = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; u < ncold; u += gs)
+    cold_ids[u] = ws.fst[u];
 }
 
 // Row copy between host table and staging rows: TO_HOST = 0 copies
@@ -346,16 +386,18 @@ extern "C" hl_status hl_cold_plan(hl_handle* h, const uint32_t* gids, int32_t* c
   const uint32_t n = (uint32_t)n_lookups;
   // selection: the first n_sel_max samples (no list) or the listed ones; an
   // empty selection inserts nothing
-  // (a sample of about 100 lookups or more: a block's threads, else a wave's)
-  const int32_t tps = n_lookups > 96ll * n_samples ? 256 : 64;
+  int32_t tps = 8;
+  while (tps < 256 && (int64_t)tps * n_samples < n_lookups) tps *= 2;
+  uint32_t parts = 1;  // blocks per listed sample: 1024 lookups each on average, at most 1024 of them
+  if (sample_ids && n_samples > 0) parts = (uint32_t)std::min<int64_t>(1 + n_lookups / (1024ll * n_samples), 1024);
   const cg_sel sel{sample_ids, n_sel_dev, n_sel_max, n_samples, bps, tps, (int64_t)n_sel_max * bps};
   uint32_t ib = 0;
   if (n > 0 && n_sel_max > 0) {
     const uint64_t listed = std::min(n_sel_max, std::max(n_samples, 1));  // (a longer list: cg_lookups)
-    ib = sample_ids ? std::min(hl_div_up(listed * tps, 256), 1u << 20) : hl_div_up(n, 256);
+    ib = sample_ids ? std::min(hl_div_up(listed * tps, 256), 1u << 16) : hl_div_up(n, 256);
   }
   if (ib > 0)
-    HL_KERNEL(h, s, "cg_insert", cg_insert, dim3(ib), dim3(256), 0, s, gids, codes, bag_ptr, sel, n, h->n_rows, table, ws,
+    HL_KERNEL(h, s, "cg_insert", cg_insert, dim3(ib, parts), dim3(256), 0, s, gids, codes, bag_ptr, sel, n, h->n_rows, table, ws,
               h->d_err);
   // the insert kernel cleared the status words, so one fixed tag serves every
   // call (and every replay of a captured graph)
@@ -363,7 +405,7 @@ extern "C" hl_status hl_cold_plan(hl_handle* h, const uint32_t* gids, int32_t* c
   HL_KERNEL(h, s, "cg_rank", cg_rank, dim3(ws.rtiles), dim3(CG_RT_THREADS), 0, s, gids, codes, ib > 0 ? n : 0u, table, ws,
             n_cold_dev, epoch, nullptr, 0, 0, h->d_err);
   if (ib > 0)
-    HL_KERNEL(h, s, "cg_codes", cg_codes, dim3(ib), dim3(256), 0, s, bag_ptr, sel, n, table, ws, cap, h->k_cap, codes,
+    HL_KERNEL(h, s, "cg_codes", cg_codes, dim3(ib, parts), dim3(256), 0, s, bag_ptr, sel, n, table, ws, cap, h->k_cap, codes,
               cold_ids_out, h->d_err);
   HL_LAUNCHED();
   return HL_OK;

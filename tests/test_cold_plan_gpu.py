@@ -59,6 +59,39 @@ def test_cold_plan_selection(B, bps, mean, how):
         h.close()
 
 
+@pytest.mark.parametrize("B,bps,base,long", [
+    (1, 1, 33, 0), (3, 2, 4000, 0), (40, 3, 11, 40), (64, 2, 0, 17), (300, 1, 1, 33), (200, 1, 1, 6000), (9, 2, 600, 9000)])
+def test_cold_plan_long_samples(B, bps, base, long):
+    """Listed samples of very different lengths: about 8 to 256 threads a sample,
+    samples past 4 lookups per thread by the block, several blocks a sample."""
+    rng = np.random.default_rng(B + base)
+    n_bags, n_rows, k_cap = B * bps, 20_000, 2_000
+    lens = np.full(n_bags, base)
+    lens[::7] = np.maximum(lens[::7], long)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(ptr[-1])
+    hot = np.sort(rng.permutation(n_rows)[:k_cap]).astype(np.uint32)
+    gids = rng.integers(0, n_rows, n).astype(np.uint32)
+    gids[rng.random(n) < 0.5] = 7
+    codes = O.remap(hot, gids).astype(np.int32)
+    sel = np.sort(rng.permutation(B)[:max(1, (2 * B) // 3)]).astype(np.int32)
+    want_cold, want_codes = O.cold_plan(gids, codes.copy(), ptr, sel, sel.size, bps, k_cap)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int32)).cuda()
+    h = hl.hl_create(np.array([n_rows], np.uint32), 4, "f32", k_cap)
+    try:
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, n_bags, B), dtype=torch.uint8, device="cuda")
+        cold, nc = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        for _ in range(2):
+            dc = d(codes)
+            hl.hl_cold_plan(h, d(gids), dc, d(ptr), B, bps, n, d(sel), None, sel.size, n, cold, nc, ws)
+            assert int(nc.item()) == want_cold.size
+            assert np.array_equal(u32(cold[:want_cold.size]), want_cold)
+            assert np.array_equal(dc.cpu().numpy(), want_codes)
+        assert hl.hl_last_device_error(h) == 0
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("n_max", [200, 1 << 26, 2**31 - 1])
 @pytest.mark.parametrize("mean", [1, 120])
 def test_cold_plan_loose_bound(n_max, mean):
