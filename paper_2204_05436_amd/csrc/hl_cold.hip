@@ -392,8 +392,9 @@ extern "C" hl_status hl_cold_plan(hl_handle* h, const uint32_t* gids, int32_t* c
   if (sample_ids && n_samples > 0) parts = (uint32_t)std::min<int64_t>(1 + n_lookups / (1024ll * n_samples), 1024);
   const cg_sel sel{sample_ids, n_sel_dev, n_sel_max, n_samples, bps, tps, (int64_t)n_sel_max * bps};
   uint32_t ib = 0;
-  if (n > 0 && n_sel_max > 0) {
+  if (n_sel_max > 0) {
     const uint64_t listed = std::min(n_sel_max, std::max(n_samples, 1));  // (a longer list: cg_lookups)
+    // (a list is looked through for ids that name no sample also where there are no lookups)
     ib = sample_ids ? std::min(hl_div_up(listed * tps, 256), 1u << 16) : hl_div_up(n, 256);
   }
   if (ib > 0)
@@ -404,7 +405,7 @@ extern "C" hl_status hl_cold_plan(hl_handle* h, const uint32_t* gids, int32_t* c
   const uint32_t epoch = 1;
   HL_KERNEL(h, s, "cg_rank", cg_rank, dim3(ws.rtiles), dim3(CG_RT_THREADS), 0, s, gids, codes, ib > 0 ? n : 0u, table, ws,
             n_cold_dev, epoch, nullptr, 0, 0, h->d_err);
-  if (ib > 0)
+  if (ib > 0 && n > 0)
     HL_KERNEL(h, s, "cg_codes", cg_codes, dim3(ib, parts), dim3(256), 0, s, bag_ptr, sel, n, table, ws, cap, h->k_cap, codes,
               cold_ids_out, h->d_err);
   HL_LAUNCHED();

@@ -127,3 +127,20 @@ def test_cold_plan_loose_bound(n_max, mean):
         assert hl.hl_last_device_error(h) == hl.DEVERR["OUT_OF_RANGE"]
     finally:
         h.close()
+
+
+def test_cold_plan_list_without_lookups():
+    """A mini-batch of empty bags: no cold rows, and a listed id that names no
+    sample is still reported."""
+    h = hl.hl_create(np.array([10], np.uint32), 4, "f32", 4)
+    try:
+        z = lambda n: torch.zeros(n, dtype=torch.int32, device="cuda")
+        ws = torch.zeros(hl.hl_workspace_bytes(h, 1, 6, 3), dtype=torch.uint8, device="cuda")
+        for ids, err in (([0, 2], 0), ([2, 3], hl.DEVERR["OUT_OF_RANGE"]), ([-1, 0], hl.DEVERR["OUT_OF_RANGE"])):
+            nc = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+            sel = torch.tensor(ids, dtype=torch.int32, device="cuda")
+            hl.hl_cold_plan(h, z(1), z(1), z(7), 3, 2, 0, sel, None, 2, 0, None, nc, ws)
+            assert int(nc.item()) == 0
+            assert hl.hl_last_device_error(h) == err
+    finally:
+        h.close()
