@@ -61,12 +61,14 @@ eb_fwd_oh(const void* w_hot, const void* stg, int32_t stg_rows, uint32_t n_hot, 
 }
 
 // The forward over every bag of a one-hot mini-batch and the backward's
-// grouping in one launch: the first T blocks each sort a table (gt_sort_body),
-// the others pool the bags and check that every bag is one-hot.  Nothing one side
+// grouping in one launch: T blocks each sort a table (gt_sort_body), the others
+// pool the bags and check that every bag is one-hot.  Nothing one side
 // writes is read by the other, so they run side by side (the sorts on a few
 // compute units at LDS and latency speed, the HBM-bound forward on the rest).
 // CODES: the sorts read the slot codes themselves, T apart, which spares the
-// launch of gt_prep (GT_CODES_E); otherwise gt_prep's keys.
+// launch of gt_prep (GT_CODES_E); otherwise gt_prep's keys.  The first T blocks
+// sort; with CODES the first T + GT_CHECKS take tickets, of which the first
+// GT_CHECKS check the bags and then pool.
 template <int VEC, bool BF, int ITEMS, bool CODES>
 __global__ void __launch_bounds__(GT_THREADS)
 eb_fwd_gt(const void* w_hot, const void* stg, int32_t stg_rows, uint32_t n_hot, uint32_t k_cap,
@@ -74,13 +76,25 @@ eb_fwd_gt(const void* w_hot, const void* stg, int32_t stg_rows, uint32_t n_hot, 
           int64_t n_lookups, int64_t n_bags, gt_src src, uint32_t E, int32_t T, const uint32_t* __restrict__ tb,
           uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t* err, int ballot_only, hl_hook hk) {
   __shared__ uint32_t s_code[GT_WAVES][OH_UNIT];
+  __shared__ uint32_t s_ticket[2];
   hl_hook_head(hk);
-  if (blockIdx.x < (uint32_t)T) {
-    gt_sort_body<ITEMS, CODES>(blockIdx.x, src, E, T, (uint32_t)n_bags, tb, n_hot, kout, vout, err, ballot_only);
-  } else {
-    eb_fwd_oh_body<VEC, BF, 0>(blockIdx.x - T, gridDim.x - T, w_hot, stg, stg_rows, n_hot, k_cap, codes, bag_ptr,
-                               out, g, n_lookups, n_bags, err, s_code, 0, INT64_MAX, true);
+  const uint32_t first = CODES ? (uint32_t)T + GT_CHECKS : (uint32_t)T, nblk = gridDim.x - (uint32_t)T;
+  uint32_t t = blockIdx.x, epoch = 0, bid = blockIdx.x - first;
+  if (CODES && blockIdx.x < first) {
+    if (threadIdx.x == 0) s_ticket[0] = hl_ticket(src.ticket, first, &s_ticket[1]);
+    __syncthreads();
+    t = s_ticket[0] - GT_CHECKS;  // (a check: past every table)
+    epoch = s_ticket[1];
+    if (s_ticket[0] < GT_CHECKS) {
+      gt_check_bags(s_ticket[0], src, (uint32_t)n_bags, epoch);
+      bid = nblk - GT_CHECKS + s_ticket[0];  // (the last to pool: a small mini-batch takes few blocks)
+    }
   }
+  if (t < (uint32_t)T)
+    gt_sort_body<ITEMS, CODES>(t, epoch, src, E, T, (uint32_t)n_bags, tb, n_hot, kout, vout, err, ballot_only);
+  else
+    eb_fwd_oh_body<VEC, BF, 0>(bid, nblk, w_hot, stg, stg_rows, n_hot, k_cap, codes, bag_ptr, out, g,
+                               n_lookups, n_bags, err, s_code, 0, INT64_MAX, true);
 }
 
 // ----------------------------------------------------------------------------- backward
@@ -1087,14 +1101,16 @@ static void launch_fwd_gt(hl_handle* h, hipStream_t s, const void* w_hot, const 
   // one block per compute unit (each holds the sort's LDS): the tables' sorts
   // and, on the other units, the forward
   const int cus = eb_device_cus(h);
-  const uint32_t nf = (uint32_t)(cus > 2 * T ? cus - T : cus);
+  const uint32_t nf = (uint32_t)std::max(cus > 2 * T ? cus - T : cus, GT_CHECKS);
   const hl_hook hk = hl_hook_take(h);
   gt_src src{};
   if (E <= GT_CODES_E) {
     src.codes = codes;
+    src.bag_ptr = bag_ptr;
     src.k_cap = h->k_cap;
     src.stg_rows = stg_rows;
     src.ticket = (uint32_t*)workspace + HL_HDR_GT;
+    src.bad = (uint64_t*)((uint32_t*)workspace + HL_HDR_GBAD);
     src.st = (uint64_t*)((uint32_t*)workspace + HL_HDR_GSTAT);
   } else {
     src.keys_tm = k_tm;

@@ -133,7 +133,7 @@ gt_sort(const uint32_t* __restrict__ keys_tm, const uint32_t* __restrict__ cum, 
   src.keys_tm = keys_tm;
   src.cum = cum;
   src.nblk = nblk;
-  gt_sort_body<ITEMS, false>(blockIdx.x, src, E, T, n, tb, n_hot, kout, vout, err, ballot_only);
+  gt_sort_body<ITEMS, false>(blockIdx.x, 0, src, E, T, n, tb, n_hot, kout, vout, err, ballot_only);
 }
 
 // ----------------------------------------------------------------------------- host

@@ -39,20 +39,54 @@ __device__ __forceinline__ uint32_t gt_scan(uint32_t v, uint32_t* ws, uint32_t* 
 // Where a table's sort takes its keys: from gt_prep (table-major keys, and per
 // prep block the hot keys of the tables before each), or (codes not NULL) from
 // the slot codes themselves, with the hot keys of the earlier tables published
-// by their blocks (the table by ticket, so those are running).
+// by their blocks (the table by ticket, so those are running).  From the codes,
+// the launch's first GT_CHECKS tickets check that every bag holds its own lookup
+// alone, a slice of the offsets each, and publish what they found; a sort looks at
+// it when it is done and, if some bag does not, sorts again without the lookups of
+// such bags (as gt_prep skips them), each with its bag's offsets.  (Every sort
+// reading them from the start: 8 tables of 1024 lookups as fast as without a check,
+// 26 of 4096 2.9 us slower, since each lane's pair is a cache line of its own, as
+// its code is; like this both as fast as without a check.)
+#define GT_CHECKS 8
 struct gt_src {
   const uint32_t *keys_tm, *cum;
   uint32_t nblk;
-  const int32_t* codes;
+  const int32_t *codes, *bag_ptr;
   uint32_t k_cap;
   int32_t stg_rows;
-  uint32_t* ticket;  // header words: hl_ticket, and the published words
-  uint64_t* st;
+  uint32_t* ticket;     // header words: hl_ticket, and the published words
+  uint64_t *st, *bad;
 };
 
-// Sorts a table (a block of GT_THREADS threads): table tb_index, or by ticket.
+// (CODES) block i of GT_CHECKS: are bag_ptr[j] = j for its slice of the n + 1 offsets?
+__device__ __forceinline__ void gt_check_bags(uint32_t i, const gt_src& src, uint32_t n, uint32_t epoch) {
+  const uint32_t per = (n + GT_CHECKS) / GT_CHECKS, j1 = min((i + 1) * per, n + 1);
+  bool bad = false;
+  for (uint32_t j0 = i * per + threadIdx.x; j0 < j1; j0 += 4 * GT_THREADS) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t j = min(j0 + u * GT_THREADS, j1 - 1);
+      bad = bad || src.bag_ptr[j] != (int32_t)j;
+    }
+  }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) hl_st_store(src.bad + i, hl_st_pack(epoch, bad ? HL_ST_PRE : HL_ST_AGG, 0));
+}
+// The published word at p of this epoch whose flag is at least `least`, waited for.
+__device__ __forceinline__ uint64_t gt_wait(const uint64_t* p, uint32_t epoch, uint64_t least, uint32_t* err) {
+  for (uint32_t spins = 0;;) {
+    const uint64_t wd = hl_st_load(p);
+    if ((uint32_t)(wd >> 32) == epoch && ((wd >> 30) & 3ull) >= least) return wd;
+    if (++spins > HL_SPIN_LIMIT) {
+      hl_flag(err, HL_DEVERR_STALL);
+      return 0;
+    }
+  }
+}
+
+// Sorts table t (a block of GT_THREADS threads; epoch: CODES).
 template <int ITEMS, bool CODES>
-__device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& src, uint32_t E, int32_t T, uint32_t n,
+__device__ __forceinline__ void gt_sort_body(uint32_t t, uint32_t epoch, const gt_src& src, uint32_t E, int32_t T, uint32_t n,
                                              const uint32_t* __restrict__ tb, uint32_t n_hot,
                                              uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, uint32_t* err,
                                              int ballot_only) {
@@ -62,19 +96,8 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
   __shared__ uint32_t wcnt[GT_WAVES][GT_NB];
   __shared__ uint32_t dofs[GT_NB];
   __shared__ uint32_t scan_ws[GT_WAVES];
-  __shared__ uint32_t s_max, s_sent, s_hb, s_ht, s_table, s_epoch;
+  __shared__ uint32_t s_max, s_sent, s_hb, s_ht, s_bad;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  uint32_t t = tb_index, epoch = 0;
-  if constexpr (CODES) {
-    if (tid == 0) {
-      uint32_t e;
-      s_table = hl_ticket(src.ticket, (uint32_t)T, &e);
-      s_epoch = e;
-    }
-    __syncthreads();
-    t = s_table;
-    epoch = s_epoch;
-  }
   const uint32_t* __restrict__ keys_tm = src.keys_tm;
   const uint32_t* __restrict__ cum = src.cum;
   const uint32_t nblk = CODES ? 0u : src.nblk;
@@ -109,7 +132,9 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
   for (int j = tid; j < GT_WAVES * GT_NB; j += GT_THREADS) (&wcnt[0][0])[j] = 0;
   __syncthreads();
   const uint64_t lt = (1ull << lane) - 1ull;
-  for (int stable = ballot_only ? 1 : 0, fresh = 1; stable < 2; ++stable, fresh = 0) {
+  bool foreign = false;
+  // count: this run counts the hot keys; check (CODES): without misfit bags' lookups
+  for (bool stable = ballot_only, fresh = true, count = true, check = false;; fresh = false) {
     if (!fresh) {
       // (sorting again: the keys as loaded)
 #pragma unroll
@@ -122,8 +147,9 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
     // compressed: hot slot - lo, or R + staging row, or (skipped: an invalid
     // code, or a hot slot of another table's row) one past the largest
     uint32_t kmax = 0;
-    bool foreign = false, anysent = false;
+    bool anysent = false;
     uint32_t nhot = 0;
+    foreign = false;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
       const uint32_t ps = (uint32_t)w * (ITEMS * 64) + k * 64 + lane;
@@ -131,7 +157,11 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
       uint32_t kk = key[k];
       if constexpr (CODES) {
         kk = bw_key(kk, n_hot, src.k_cap, src.stg_rows);
-        if (valid && kk == EB_SENT) foreign = true;  // (a code that names no row)
+        const uint32_t j = min(ps, E - 1) * (uint32_t)T + t;
+        if (check && (src.bag_ptr[j] != (int32_t)j || src.bag_ptr[j + 1] != (int32_t)(j + 1)))
+          kk = EB_SENT;  // (the forward reports it)
+        else if (kk == EB_SENT)
+          foreign = true;  // (a code that names no row)
       }
       uint32_t c = EB_SENT;
       if (kk < n_hot) {
@@ -148,18 +178,17 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
       if (valid && c != EB_SENT) kmax = max(kmax, c);
       anysent = anysent || (valid && c == EB_SENT);
     }
-    if (foreign && fresh) hl_flag(err, HL_DEVERR_BAD_CODE);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor(kmax, o));
     if (lane == 0) atomicMax(&s_max, kmax);
     if (anysent) s_sent = 1;
     if constexpr (CODES) {
-      if (fresh) {
+      if (count) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) nhot += __shfl_xor(nhot, o);
         if (lane == 0) atomicAdd(&s_ht, nhot);
       }
-    } else if (fresh) {
+    } else if (count) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) {
         hb += __shfl_xor(hb, o);
@@ -171,7 +200,9 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
       }
     }
     __syncthreads();
-    if (CODES && fresh && tid == 0) hl_st_store(src.st + t, hl_st_pack(epoch, HL_ST_AGG, s_ht));
+    // (the count of a check run with the higher flag: waited for in its place)
+    if (CODES && count && tid == 0) hl_st_store(src.st + t, hl_st_pack(epoch, check ? HL_ST_PRE : HL_ST_AGG, s_ht));
+    count = false;
     const uint32_t sent = max(s_max + 1, R);  // after every valid key, never below R (not hot)
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k)
@@ -269,17 +300,41 @@ __device__ __forceinline__ void gt_sort_body(uint32_t tb_index, const gt_src& sr
       if (last) broken = __syncthreads_or(broken);
       else __syncthreads();
     }
-    if (stable || !broken) break;
+    if (!stable && broken) {
+      stable = true;
+    } else {
+      if constexpr (!CODES) break;
+      // the hot keys of the earlier tables, and (another wave, in the same round
+      // trip) what the checks of the bags found
+      if (w == 0) {
+        uint32_t v = 0;
+        if ((uint32_t)lane < t)
+          v = (uint32_t)gt_wait(src.st + lane, epoch, check ? HL_ST_PRE : HL_ST_AGG, err) & 0x3FFFFFFFu;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if (lane == 0) s_hb = v;
+      } else if (w == 1) {
+        const bool bad = lane < GT_CHECKS &&
+                         ((gt_wait(src.bad + lane, epoch, HL_ST_AGG, err) >> 30) & 3ull) == HL_ST_PRE;
+        const uint64_t any = __ballot(bad);
+        if (lane == 0) s_bad = any != 0;
+      }
+      __syncthreads();
+      if (check || !s_bad) break;
+      check = count = true;
+    }
+    __syncthreads();
     if (tid == 0) {
       s_max = 0;
       s_sent = 0;
+      if (count) s_ht = 0;
     }
     __syncthreads();
   }
+  if (foreign) hl_flag(err, HL_DEVERR_BAD_CODE);
   // hot pairs of this table (keys below R, sorted first): h of them, after
   // the earlier tables' H; the others before the earlier tables' E t - H
-  uint32_t H = s_hb, h = s_ht - s_hb;
-  if constexpr (CODES) H = hl_block_before(src.st, t, epoch, err);
+  const uint32_t H = s_hb, h = CODES ? s_ht : s_ht - s_hb;
   const uint64_t nb0 = (uint64_t)n - ((uint64_t)E * t - H) - (E - h);
   const uint32_t sent_key = max(s_max + 1, R);
 #pragma unroll

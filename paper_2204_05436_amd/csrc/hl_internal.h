@@ -194,6 +194,7 @@ __device__ __forceinline__ int32_t hl_hot_slot(const uint64_t* __restrict__ bm,
 #define HL_HDR_COLD 16   // 16 words: cold-gather counters
 #define HL_HDR_DISP 64   // 2 words: dispatch ticket
 #define HL_HDR_GT 72     // 2 words: ticket of the tables' sorts beside the forward
+#define HL_HDR_GBAD 80   // 8 published words (64-bit) of the checks of their bags
 #define HL_HDR_GSTAT 128 // 64 published words (64-bit) of theirs
 #define HL_HDR_DSTAT 256 // dispatch's published words (64-bit), to the header's end
 #define HL_DISP_MAX_TILES ((HL_WS_HEADER - 4 * HL_HDR_DSTAT) / 8)

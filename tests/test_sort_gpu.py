@@ -107,3 +107,43 @@ def test_forward_with_table_sorts(B, T):
             assert hl.hl_last_device_error(h) & hl.DEVERR["SHAPE"]
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("B,T", [(33, 3), (1024, 2), (1500, 5), (2049, 2), (4096, 2), (4097, 2)])
+def test_misfit_bags_are_skipped(B, T):
+    """As many lookups as bags, but some bags of two lookups or none: the
+    grouping that hl_embbag_fwd_plan leaves is the one of hl_embbag_bwd_plan,
+    which skips the lookups of such bags (and a code that names no row), with
+    the same errors reported."""
+    rng = np.random.default_rng(B + T)
+    dim, n, n_hot, n_stg = 8, B * T, 40 * T, 100
+    h = hl.hl_create(np.full(T, 50, np.uint32), dim, "f32", 50 * T)
+    try:
+        k_cap = 50 * T
+        hot = (np.arange(n_hot) // 40 * 50 + np.arange(n_hot) % 40).astype(np.int32)  # 40 hot rows a table
+        hl.hl_set_hot(h, torch.from_numpy(hot).cuda(), n_hot)
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, n, B), dtype=torch.uint8, device="cuda")
+        w = torch.randn((n_hot + n_stg, dim), device="cuda")
+        out = torch.zeros((n, dim), device="cuda")
+        codes = np.where(rng.random(n) < 0.8, rng.integers(0, 40, n) + 40 * (np.arange(n) % T),
+                         k_cap + rng.integers(0, n_stg, n)).astype(np.int32)
+        codes[n // 3] = k_cap + n_stg
+        ptr = np.arange(n + 1, dtype=np.int32)
+        ptr[[1, n // 2, n // 2 + 1, n - 1]] += 1
+        dc, dp = torch.from_numpy(codes).cuda(), torch.from_numpy(ptr).cuda()
+        i32 = lambda: torch.zeros(n, dtype=torch.int32, device="cuda")
+        k1, b1, k2, b2 = i32(), i32(), i32(), i32()
+        hl.hl_embbag_bwd_plan(h, n_stg, dc, dp, B, T, n, None, None, B, ws)
+        e1 = hl.hl_last_device_error(h)
+        hl.hl_embbag_bwd_grouping(h, n_stg, B, T, n, ws, k1, b1)
+        hl.hl_embbag_fwd_plan(h, w[:n_hot], w[n_hot:], n_stg, dc, dp, B, T, n, out, ws)
+        e2 = hl.hl_last_device_error(h)
+        hl.hl_embbag_bwd_grouping(h, n_stg, B, T, n, ws, k2, b2)
+        assert e1 == e2 == hl.DEVERR["SHAPE"] | hl.DEVERR["BAD_CODE"]
+        assert torch.equal(k1, k2)
+        used = k1 != -1
+        assert torch.equal(b1[used], b2[used])
+        good = (ptr[:-1] == np.arange(n)) & (ptr[1:] == np.arange(1, n + 1)) & (codes != k_cap + n_stg)
+        assert int(used.sum()) == int(good.sum())
+    finally:
+        h.close()
