@@ -354,6 +354,10 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
   }
   __syncthreads();
   const uint32_t tile = s_tile, epoch = s_epoch;
+  if (tile >= gridDim.x) {  // (hl_ticket)
+    if (tid == 0) hl_flag(err, HL_DEVERR_INTERNAL);
+    return;
+  }
   const int64_t s0 = (int64_t)tile * spb;
   const int ns = (int)min((int64_t)spb, (int64_t)n_samples - s0);
   const int64_t bg0 = s0 * bps;

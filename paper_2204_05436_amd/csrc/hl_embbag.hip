@@ -83,6 +83,10 @@ eb_fwd_gt(const void* w_hot, const void* stg, int32_t stg_rows, uint32_t n_hot, 
   if (CODES && blockIdx.x < first) {
     if (threadIdx.x == 0) s_ticket[0] = hl_ticket(src.ticket, first, &s_ticket[1]);
     __syncthreads();
+    if (s_ticket[0] >= first) {  // (hl_ticket)
+      if (threadIdx.x == 0) hl_flag(err, HL_DEVERR_INTERNAL);
+      return;
+    }
     t = s_ticket[0] - GT_CHECKS;  // (a check: past every table)
     epoch = s_ticket[1];
     if (s_ticket[0] < GT_CHECKS) {

@@ -515,7 +515,9 @@ __device__ __forceinline__ uint64_t hl_st_load(const uint64_t* p) {
 // A ticket of a launch of `n` takers and the call's epoch, in one 64-bit word
 // (epoch over the tickets handed out, in the workspace header): the taker of the
 // last ticket resets the tickets and advances the epoch for the next call, so
-// published words tagged with the epoch need no clearing between calls.
+// published words tagged with the epoch need no clearing between calls.  In a
+// header that was not zero-filled, or that overlapping calls share, tickets may run
+// past n: the callers check theirs (HL_DEVERR_INTERNAL) before they index by it.
 __device__ __forceinline__ uint32_t hl_ticket(uint32_t* word, uint32_t n, uint32_t* epoch) {
   unsigned long long* tk = (unsigned long long*)word;
   const unsigned long long x = atomicAdd(tk, 1ull);

@@ -147,3 +147,35 @@ def test_misfit_bags_are_skipped(B, T):
         assert int(used.sum()) == int(good.sum())
     finally:
         h.close()
+
+
+def test_tickets_past_the_launch():
+    """A workspace header that is not as the calls keep it (here: tickets handed
+    out past the launch's blocks) is reported, and nothing is indexed by such a
+    ticket; after a zero fill the workspace serves again."""
+    B, T, dim = 512, 4, 8
+    n = B * T
+    h = hl.hl_create(np.full(T, 50, np.uint32), dim, "f32", 50 * T)
+    try:
+        i32 = lambda k: torch.zeros(k, dtype=torch.int32, device="cuda")
+        hl.hl_set_hot(h, torch.arange(50 * T, dtype=torch.int32, device="cuda"), 50 * T)
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, n, B), dtype=torch.uint8, device="cuda")
+        ptr = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+        rows, w, out = i32(n), torch.ones((50 * T, dim), device="cuda"), torch.zeros((n, dim), device="cuda")
+        gids, codes, flags, pop, non, cnt = i32(n), i32(n), torch.zeros(B, dtype=torch.uint8, device="cuda"), i32(B), i32(B), i32(2)
+        dispatch = lambda: hl.hl_dispatch(h, rows, ptr, B, T, n, gids, codes, flags, pop, non, cnt, ws)
+        forward = lambda: hl.hl_embbag_fwd_plan(h, w, None, 0, codes, ptr, B, T, n, out, ws)
+        dispatch()
+        forward()
+        assert hl.hl_last_device_error(h) == 0
+        for word, call in ((64, dispatch), (72, forward)):
+            ws.view(torch.int32)[word] = 5000
+            call()
+            assert hl.hl_last_device_error(h) == hl.DEVERR["INTERNAL"]
+            hl.hl_workspace_init(ws)
+            for _ in range(2):
+                call()
+                assert hl.hl_last_device_error(h) == 0
+        assert int(cnt[0]) == B and bool((out == 1).all())
+    finally:
+        h.close()
