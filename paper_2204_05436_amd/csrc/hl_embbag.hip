@@ -119,10 +119,17 @@ static uint32_t bw_tile_entries(int32_t D, int vec) {
   return (uint32_t)(RB_WAVES * g.NG * RB_EN(vec));
 }
 
-// compact: no staging-row sums (gc), for plans whose apply is whole (part 0)
+// compact: no staging-row sums (gc), for plans whose apply is whole (part 0), and
+// the tiles' sums where the sort's counts were (the sort clears or writes all that
+// it reads there, and is done with it when the apply starts)
 static void bw_carve(hl_carver& c, bw_ws& ws, uint32_t n_max, int64_t max_bags, int32_t D, bool compact = false) {
-  hl_sort_ws_carve(c, ws.sort, n_max);
+  hl_sort_ws_carve_pairs(c, ws.sort, n_max);
+  if (!compact) hl_sort_ws_carve_counts(c, ws.sort);
   ws.mask = c.take<uint8_t>((size_t)max_bags + 1);
+  const size_t shared = c.off;
+  if (compact) hl_sort_ws_carve_counts(c, ws.sort);
+  const size_t counts_end = c.off;
+  if (compact) c.off = shared;
   // the smallest tile (largest count) over the vector widths the call may pick
   uint32_t te = bw_tile_entries(D, 1);
   uint32_t te2 = bw_tile_entries(D, D % 2 == 0 ? 2 : 1), te4 = bw_tile_entries(D, D % 4 == 0 ? 4 : 1);
@@ -136,6 +143,7 @@ static void bw_carve(hl_carver& c, bw_ws& ws, uint32_t n_max, int64_t max_bags, 
   ws.gc_rows = compact ? 0 : n_max;
   ws.gc = c.take<float>((size_t)ws.gc_rows * D);
   ws.bnd = c.take<uint32_t>(1);
+  c.off = std::max(c.off, counts_end);
 }
 
 size_t hl_bwd_ws_bytes(const hl_handle* h, int64_t max_lookups, int64_t max_bags) {

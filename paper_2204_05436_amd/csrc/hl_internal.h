@@ -397,6 +397,10 @@ struct hl_sort_ws {
 };
 
 void hl_sort_ws_carve(hl_carver& c, hl_sort_ws& ws, uint32_t n_max);
+// its two parts: the pairs, which hold the result, and what only the sort itself
+// uses (it needs no particular contents)
+void hl_sort_ws_carve_pairs(hl_carver& c, hl_sort_ws& ws, uint32_t n_max);
+void hl_sort_ws_carve_counts(hl_carver& c, hl_sort_ws& ws);
 // Sorts ws.k0/ws.v0 (first *n_dev items if n_dev != NULL, else n_host) by the
 // low `bits` bits of the key; returns in *out_k/*out_v the buffers holding the
 // result.  Keys must be < 2^bits - 1 except the all-ones sentinel, which sorts

@@ -42,6 +42,11 @@
 #include "hl_sort_pass.h"
 
 void hl_sort_ws_carve(hl_carver& c, hl_sort_ws& ws, uint32_t n_max) {
+  hl_sort_ws_carve_pairs(c, ws, n_max);
+  hl_sort_ws_carve_counts(c, ws);
+}
+
+void hl_sort_ws_carve_pairs(hl_carver& c, hl_sort_ws& ws, uint32_t n_max) {
   ws.n_max = n_max;
   // (fewer items per thread than 8 only up to HL_SORT_TILES_AIM tiles)
   ws.tiles_max = std::max({std::min(hl_div_up(n_max, HL_SORT_TILE_MIN), (uint32_t)HL_SORT_TILES_AIM),
@@ -50,12 +55,15 @@ void hl_sort_ws_carve(hl_carver& c, hl_sort_ws& ws, uint32_t n_max) {
   ws.v0 = c.take<uint32_t>(n_max);
   ws.k1 = c.take<uint32_t>(n_max);
   ws.v1 = c.take<uint32_t>(n_max);
+  ws.ctr = c.base ? c.header() + HL_HDR_SORT : nullptr;
+}
+
+void hl_sort_ws_carve_counts(hl_carver& c, hl_sort_ws& ws) {
   ws.tot = c.take<uint32_t>((size_t)HL_SORT_MAXPASS * HL_SORT_MAXNB);
   for (int i = 0; i < 4; ++i) ws.row[i] = c.take<uint32_t>((size_t)ws.tiles_max * (HL_SORT_MAXNB / 2));
   for (int i = 0; i < 2; ++i)
     ws.grp[i] = c.take<uint64_t>((size_t)hl_div_up(ws.tiles_max, HL_SORT_GRP) * (HL_SORT_MAXNB / 2));
   ws.gtot = c.take<uint64_t>(HL_SORT_MAXNB / 2);
-  ws.ctr = c.base ? c.header() + HL_HDR_SORT : nullptr;
 }
 
 static srt_plan srt_make_plan(int bits) {

@@ -2,8 +2,9 @@
 static device array) against hl_embbag_bwd_sgd with a caller's workspace, on
 the same inputs, through the C ABI: the updated hot and staging rows bit for
 bit (same kernels, same grouping), on two calls in a row, the second with a
-smaller mini-batch (the array keeps the first call's contents), and a
-mini-batch too large for the array refused with HL_ERR_CAPACITY."""
+smaller mini-batch (the array keeps the first call's contents), mini-batches
+that nearly fill the array, and one too large for it refused with
+HL_ERR_CAPACITY."""
 import dataclasses
 
 import numpy as np
@@ -74,3 +75,29 @@ def test_noalloc_matches_workspace_backward(name):
     finally:
         hp.close()
         table.close()
+
+
+@pytest.mark.parametrize("dim,n", [(192, 215_604), (256, 168_756), (320, 138_648), (384, 117_632), (1024, 46_784)])
+def test_noalloc_largest(dim, n):
+    """Mini-batches of one lookup per bag that nearly fill the 32 MiB: accepted,
+    with the same rows as the workspace form, twice in a row (the second call
+    finds the first one's tile sums where its sort keeps counts)."""
+    rng = np.random.default_rng(dim)
+    n_hot, n_stg = 1000, 700
+    h = hl.hl_create(np.array([5000], np.uint32), dim, "f32", n_hot)
+    try:
+        hl.hl_set_hot(h, torch.arange(n_hot, dtype=torch.int32, device="cuda"), n_hot)
+        g = rng.zipf(1.2, n) % (n_hot + n_stg)
+        codes = torch.from_numpy(g.astype(np.int32)).cuda()  # (k_cap = n_hot: row g of the two together)
+        ptr = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+        dY = torch.randn((n, dim), device="cuda")
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, n, n), dtype=torch.uint8, device="cuda")
+        a = torch.randn((n_hot + n_stg, dim), device="cuda")
+        b = a.clone()
+        for _ in range(2):
+            hl.hl_embbag_bwd_sgd(h, a[:n_hot], a[n_hot:], n_stg, codes, ptr, n, 1, n, None, None, n, dY, 0.01, ws)
+            hl.hl_embbag_bwd_sgd_noalloc(h, b[:n_hot], b[n_hot:], n_stg, codes, ptr, n, 1, n, None, None, n, dY, 0.01)
+            assert hl.hl_last_device_error(h) == 0
+            assert torch.equal(a, b)
+    finally:
+        h.close()
