@@ -1,6 +1,8 @@
 // Popularity classification, mu-batch partition (stable compaction), the
 // gid -> hot-slot remap, and the dispatch kernel that does all of them (with
 // the address generation) in one pass.
+#include <algorithm>
+
 #include "hl_internal.h"
 
 // ----------------------------------------------------------------------------- classify
@@ -484,31 +486,28 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
 }
 
 // the samples per block of the fused dispatch, or 0 when it takes the step by
-// step calls (which does not depend on cus, the compute units of the call's
-// stream).  More blocks spread the random probes (a compute unit takes one cache
+// step calls.  More blocks spread the random probes (a compute unit takes one cache
 // line a cycle), but every block's ticket is an atomic on one word: 212,992
 // lookups took 12.7 us with about 64 or 96 blocks aimed at, 11.8 with 128, 11.5
 // with 160, 12.0 with 192, 12.3 with 256 (15.0 with 104 blocks, a look-back
 // through inclusive prefixes and a second counter for the call's end); batch
 // 32768 26.9 -> 20.5 with 208 blocks of 4096 lookups (416 of 2048: 22.4).  About
-// 64 on a stream of few compute units, where more blocks only queue.
+// 64 on a stream of few compute units (cus), where more blocks only queue, while
+// their published words have room; past that as on a wide stream, so whether the
+// dispatch is fused does not depend on the stream (the wide sizing has room
+// wherever the other has: fewer, larger blocks, and the same caps).
 static int64_t ds_spb(const hl_handle* h, int32_t n_samples, int32_t bps, int64_t n_lookups, const void* workspace,
                       size_t ws_bytes, int cus) {
   if (n_samples == 0 || bps > DS_MAX_BAGS || h->n_tables > DS_MAX_TABLES || !workspace || ws_bytes < HL_WS_HEADER)
     return 0;
-  for (int64_t aim : {DS_BLOCKS_WIDE, DS_BLOCKS_AIM}) {
-    if (aim == DS_BLOCKS_WIDE && cus <= DS_BLOCKS_WIDE) continue;
-    int64_t lpb = n_lookups / aim;
-    const int64_t most = aim == DS_BLOCKS_WIDE ? 2 * DS_LOOKUPS_MAX : DS_LOOKUPS_MAX;
-    lpb = lpb < DS_LOOKUPS_MIN ? DS_LOOKUPS_MIN : (lpb > most ? most : lpb);
+  auto sized = [&](int64_t aim, int64_t most) {  // 0: more blocks than words
+    const int64_t lpb = std::min(std::max<int64_t>(n_lookups / aim, DS_LOOKUPS_MIN), most);
     int64_t spb = n_lookups > 0 ? (lpb * n_samples + n_lookups - 1) / n_lookups : DS_MAX_SPB;
-    const int64_t bag_cap = DS_MAX_BAGS / bps;
-    if (spb > bag_cap) spb = bag_cap;
-    if (spb > DS_MAX_SPB) spb = DS_MAX_SPB;
-    if (spb < 1) spb = 1;
-    if ((n_samples + spb - 1) / spb <= HL_DISP_MAX_TILES) return spb;
-  }
-  return 0;
+    spb = std::max<int64_t>(std::min<int64_t>({spb, DS_MAX_BAGS / bps, DS_MAX_SPB}), 1);
+    return (n_samples + spb - 1) / spb <= HL_DISP_MAX_TILES ? spb : 0;
+  };
+  const int64_t spb = cus > DS_BLOCKS_WIDE ? 0 : sized(DS_BLOCKS_AIM, DS_LOOKUPS_MAX);
+  return spb ? spb : sized(DS_BLOCKS_WIDE, 2 * DS_LOOKUPS_MAX);
 }
 
 bool hl_dispatch_fused(const hl_handle* h, int32_t n_samples, int32_t bps, int64_t n_lookups, const void* workspace,
