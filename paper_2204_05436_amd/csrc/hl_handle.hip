@@ -285,22 +285,29 @@ extern "C" hl_status hl_host_free(void* host) {
 }
 
 // ----------------------------------------------------------------------------- gids
-// A wave takes GIDS_BAGS consecutive bags, whose lookups are contiguous: lane j
-// holds the offset of bag j, and each lookup's bag is found by binary search over
-// the lanes' offsets (shuffles; no LDS, no barrier), four lookups per lane at a
-// time with their row loads issued together.  (The call knows bags, not lookups:
-// 32 bags give a wave of one-lookup bags half its lanes, one of 20-lookup bags
-// ten rounds of lanes.)  Bound by latency: offsets, rows, ids.  A block of 256
-// threads per 64 bags took 4.5 us for 212,992 single lookups and 7.2 for 328,000
-// in bags of 20, this 4.2
-// and 6.7.
+// A group of GIDS_BAGS consecutive bags, whose lookups are contiguous, by one
+// wave or by several in turn: lane j holds the offset of bag j, and each lookup's
+// bag is found by binary search over the lanes' offsets (shuffles; no LDS, no
+// barrier), four lookups per lane at a time with their row loads issued together.
+// The call knows bags, not lookups: groups of 32 bags give a wave of one-lookup
+// bags half its lanes, one of 20-lookup bags ten rounds of lanes, and where there
+// are few groups up to GIDS_PARTS waves share each (GIDS_WAVES in all), since then
+// the bags may be of any length.  Bound by latency: offsets, rows, ids.  A block
+// of 256 threads per 64 bags took 4.5 us for 212,992 single lookups and 7.2 for
+// 328,000 in bags of 20, a wave per group 4.2 and 6.7.  Back to back: 4 bags of
+// 20,000 135 us with the block, 400 with one wave, 9 with several; one bag of
+// 200,000 237, 998 and 20; 320 bags of 3000 517, 502 and 11.
 #define GIDS_BAGS 32
+#define GIDS_PARTS 64
+#define GIDS_WAVES 2048
 __global__ void __launch_bounds__(256)
-hl_k_gids(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr, int64_t n_bags,
+hl_k_gids(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr, int64_t n_bags, int32_t parts,
           const uint32_t* __restrict__ base, const uint32_t* __restrict__ nrow, int32_t n_tables,
           uint32_t* __restrict__ gids, uint32_t* err) {
   const int lane = threadIdx.x & 63;
-  const int64_t b0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * GIDS_BAGS;
+  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t b0 = wave / parts * GIDS_BAGS;
+  const int32_t part = (int32_t)(wave % parts);
   if (b0 >= n_bags) return;
   const int nb = (int)min((int64_t)GIDS_BAGS, n_bags - b0);
   const int32_t off = bag_ptr[b0 + min(lane, nb)];  // (lanes past nb: the end)
@@ -310,17 +317,17 @@ hl_k_gids(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
   const uint32_t bj = base[tj], nj = nrow[tj];
   const int32_t lo = __shfl(off, 0), hi = __shfl(off, nb);
   // 4 lookups per lane at a time, their row loads issued together
-  for (int32_t i0 = lo; i0 < hi; i0 += 256) {
+  for (int64_t i0 = (int64_t)lo + part * 256; i0 < hi; i0 += parts * 256) {
     uint32_t r[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int32_t i = i0 + k * 64 + lane;
+      const int64_t i = i0 + k * 64 + lane;
       r[k] = i < hi ? rows[i] : 0u;
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (i0 + k * 64 >= hi) break;  // (the same for every lane)
-      const int32_t i = i0 + k * 64 + lane;
+      const int64_t i = i0 + k * 64 + lane;
       int a = 0;  // the last bag that starts at or before lookup i
 #pragma unroll
       for (int s = GIDS_BAGS / 2; s > 0; s >>= 1) {
@@ -342,8 +349,10 @@ extern "C" hl_status hl_lookup_gids(const hl_handle* h, const uint32_t* rows, co
   if (n_bags == 0) return HL_OK;
   if (n_bags >= (1ll << 31)) return HL_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  HL_KERNEL(h, s, "hl_k_gids", hl_k_gids, dim3(hl_div_up(n_bags, 4 * GIDS_BAGS)), dim3(256), 0, s,
-                     rows, bag_ptr, n_bags, h->d_base, h->d_rows, h->n_tables, gids, h->d_err);
+  const uint32_t groups = hl_div_up(n_bags, GIDS_BAGS);
+  const uint32_t parts = groups >= GIDS_WAVES ? 1 : (GIDS_WAVES / groups < GIDS_PARTS ? GIDS_WAVES / groups : GIDS_PARTS);
+  HL_KERNEL(h, s, "hl_k_gids", hl_k_gids, dim3(hl_div_up((uint64_t)groups * parts, 4)), dim3(256), 0, s, rows, bag_ptr, n_bags,
+            (int32_t)parts, h->d_base, h->d_rows, h->n_tables, gids, h->d_err);
   HL_LAUNCHED();
   return HL_OK;
 }

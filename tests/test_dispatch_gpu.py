@@ -1,6 +1,7 @@
-"""The dispatch at the sizes where its blocks change: more than 2048 lookups a
-block, and mini-batches for which one sizing or both would take more blocks than
-its published words have room for.  Whether it is one launch is the same on a
+"""The address generation over bags of any length, and the dispatch at the sizes
+where its blocks change: more than 2048 lookups a block, and mini-batches for
+which one sizing or both would take more blocks than its published words have
+room for.  Whether it is one launch is the same on a
 stream of the whole GPU and on one of few compute units."""
 import numpy as np
 import pytest
@@ -54,4 +55,36 @@ def test_dispatch_block_sizes(B, T, fused):
     finally:
         hl.hl_trace_enable(h, 0)
         hl.hl_stream_destroy(few)
+        h.close()
+
+
+@pytest.mark.parametrize("T,lens", [
+    (1, [70_001]), (3, [0, 33_000, 0, 0, 7, 20_000, 0]), (5, [1000] * 31 + [0, 999]), (26, [1] * 2600),
+    (4, [300] * 33 + [0] * 40 + [5000] * 3), (2, [0, 0]), (7, [1, 2, 0] * 21_846), (3, [1, 0, 3] * 22_000)])
+def test_lookup_gids_bag_lengths(T, lens):
+    """The row-to-id kernel where several waves share 32 bags (fewer than 65,536
+    bags) and where each has its own, bags of any length; a row past its table is
+    reported and gets no id."""
+    rng = np.random.default_rng(len(lens))
+    lens = np.array(lens)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(ptr[-1])
+    rows_per = rng.integers(50, 5000, T).astype(np.uint32)
+    base = np.concatenate([[0], np.cumsum(rows_per)[:-1]])
+    t = np.repeat(np.arange(lens.size) % T, lens)
+    rows = rng.integers(0, 1 << 30, n) % rows_per[t]
+    want = (base[t] + rows).astype(np.uint32)
+    h = hl.hl_create(rows_per, 4, "f32", 10)
+    try:
+        d = lambda a: torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).cuda()
+        gids = torch.zeros(n + 5, dtype=torch.int32, device="cuda")
+        for bad in ([], [0, n // 2, n - 1]):
+            if bad and not n:
+                continue
+            for i in bad:
+                rows[i], want[i] = rows_per[t[i]], 0xFFFFFFFF
+            hl.hl_lookup_gids(h, d(np.append(rows, 0)), d(ptr), lens.size, gids)
+            assert np.array_equal(u32(gids[:n]), want) and not gids[n:].any()
+            assert hl.hl_last_device_error(h) == (hl.DEVERR["OUT_OF_RANGE"] if bad else 0)
+    finally:
         h.close()
