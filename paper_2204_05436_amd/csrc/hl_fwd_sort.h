@@ -51,7 +51,7 @@ eb_fwd_srt(srt_args a, eb_side f, hl_hook hk) {
 
 template <int VEC, bool BF>
 static void eb_fwd_srt_passes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int npasses, int b,
-                              int nb, int items, hipStream_t s, const hl_sort_side& side) {
+                              int nb, int items, hipStream_t s, const hl_hook& hk, const hl_sort_side& side) {
   eb_side f{};
   f.w_hot = side.w_hot;
   f.stg = side.stg;
@@ -75,7 +75,7 @@ static void eb_fwd_srt_passes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& s
   int p = 0;
   srt_dispatch(nb, items, [&](auto NB, auto IT) {
     constexpr int nbins = decltype(NB)::value, it = decltype(IT)::value;
-    srt_passes<nbins, it>(h, ws, src, nullptr, n, pl, hl_hook{}, [&](auto first, const srt_args& a, const hl_hook& k) {
+    srt_passes<nbins, it>(h, ws, src, nullptr, n, pl, hk, [&](auto first, const srt_args& a, const hl_hook& k) {
       f.from = total * p / npasses;
       f.to = total * (p + 1) / npasses;
       ++p;

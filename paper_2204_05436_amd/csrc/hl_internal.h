@@ -433,12 +433,11 @@ struct hl_sort_src {
 // a row type and lane width, NULL if there is none).
 struct hl_sort_side {
   void (*passes)(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int npasses, int b, int nb, int items,
-                 hipStream_t s, const hl_sort_side& side);
+                 hipStream_t s, const hl_hook& hk, const hl_sort_side& side);
   const void *w_hot, *stg;
   int32_t n_samples, bps;
   int64_t n_lookups;
   float* out;
-  int vec;
 };
 typedef decltype(hl_sort_side::passes) hl_sort_side_fn;
 hl_sort_side_fn hl_fwd_sort_side(bool bf16, int vec);

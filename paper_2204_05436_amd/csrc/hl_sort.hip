@@ -206,7 +206,7 @@ static hl_status srt_run(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, c
   else CNT(2048);
 #undef CNT
   if (side) {
-    side->passes(h, ws, src, n_host, pl.passes, pl.b, pl.nb, items, s, *side);
+    side->passes(h, ws, src, n_host, pl.passes, pl.b, pl.nb, items, s, hk, *side);
   } else {
     srt_dispatch(pl.nb, items, [&](auto NB, auto IT) {
       constexpr int nb = decltype(NB)::value, it = decltype(IT)::value;
