@@ -51,7 +51,7 @@ eb_fwd_srt(srt_args a, eb_side f, hl_hook hk) {
 
 template <int VEC, bool BF>
 static void eb_fwd_srt_passes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int npasses, int b,
-                              int nb, int items, hipStream_t s, const hl_hook& hk, const hl_sort_side& side) {
+                              int nb, int items, int cus, hipStream_t s, const hl_hook& hk, const hl_sort_side& side) {
   eb_side f{};
   f.w_hot = side.w_hot;
   f.stg = side.stg;
@@ -68,16 +68,21 @@ static void eb_fwd_srt_passes(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& s
   f.bps = side.bps;
   f.nbg = eb_bags_per_group(side.n_lookups, src.n_bags);
   f.one_hot = side.n_lookups == src.n_bags;
-  // units (of a wave) or chunks (of a row group), split evenly over the passes
+  // units (of a wave) or chunks (of a row group), split evenly over the passes;
+  // bags that fit the compute units beside the first pass all at once go there
+  // together, since each launch would last as long as its longest bag (3 bags of
+  // 80,000 lookups: 26.7 ms shared, 13.0 together)
   const int64_t total = f.one_hot ? eb_oh_units(f.g, VEC, src.n_bags) : (src.n_bags + f.nbg - 1) / f.nbg;
   const int64_t per_block = f.one_hot ? HL_SORT_WAVES : HL_SORT_WAVES * f.g.NG;
   const srt_plan pl{npasses, b, nb};
   int p = 0;
+  bool together = false;
   srt_dispatch(nb, items, [&](auto NB, auto IT) {
     constexpr int nbins = decltype(NB)::value, it = decltype(IT)::value;
     srt_passes<nbins, it>(h, ws, src, nullptr, n, pl, hk, [&](auto first, const srt_args& a, const hl_hook& k) {
-      f.from = total * p / npasses;
-      f.to = total * (p + 1) / npasses;
+      if (p == 0) together = !f.one_hot && (total + per_block - 1) / per_block <= cus - (int64_t)(a.tiles + a.sums);
+      f.from = together ? (p == 0 ? 0 : total) : total * p / npasses;
+      f.to = together ? total : total * (p + 1) / npasses;
       ++p;
       int64_t blocks = (f.to - f.from + per_block - 1) / per_block;
       if (blocks > 4096) blocks = 4096;

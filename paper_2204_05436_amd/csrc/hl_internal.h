@@ -433,7 +433,7 @@ struct hl_sort_src {
 // a row type and lane width, NULL if there is none).
 struct hl_sort_side {
   void (*passes)(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, uint32_t n, int npasses, int b, int nb, int items,
-                 hipStream_t s, const hl_hook& hk, const hl_sort_side& side);
+                 int cus, hipStream_t s, const hl_hook& hk, const hl_sort_side& side);
   const void *w_hot, *stg;
   int32_t n_samples, bps;
   int64_t n_lookups;

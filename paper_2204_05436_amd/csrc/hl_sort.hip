@@ -194,7 +194,7 @@ static hl_status srt_run(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, c
   if (n_host > ws.n_max || n_host >= (1u << 30)) return HL_ERR_CAPACITY;
   if (bits > 32) return HL_ERR_UNSUPPORTED;
   const srt_plan pl = srt_make_plan(bits);
-  const int items = srt_items(n_host, hl_stream_cus(s));
+  const int cus = hl_stream_cus(s), items = srt_items(n_host, cus);
   const hl_hook hk = hl_hook_take(h);
   const uint32_t tile = (uint32_t)(HL_SORT_THREADS * items), tiles = hl_div_up(n_host, tile);
 #define CNT(NB)                                                                                                      \
@@ -206,7 +206,7 @@ static hl_status srt_run(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, c
   else CNT(2048);
 #undef CNT
   if (side) {
-    side->passes(h, ws, src, n_host, pl.passes, pl.b, pl.nb, items, s, hk, *side);
+    side->passes(h, ws, src, n_host, pl.passes, pl.b, pl.nb, items, cus, s, hk, *side);
   } else {
     srt_dispatch(pl.nb, items, [&](auto NB, auto IT) {
       constexpr int nb = decltype(NB)::value, it = decltype(IT)::value;

@@ -34,12 +34,15 @@ def _lens(rng, layout, n):
     raise ValueError(layout)
 
 
-@pytest.mark.parametrize("n,layout,bits", [
+SIZES = [
     (1, "even", 10), (1023, "even", 9), (1025, "tail", 17), (8 * 1024, "head", 16), (8 * 1024 + 1, "even", 18),
     (9001, "one", 19), (9002, "as_many", 20), (20000, "head", 22), (20000, "tail", 24),
     (128 * 1024, "even", 18), (128 * 1024 + 1, "even", 20), (128 * 2048 + 1, "tail", 21), (128 * 2048, "one", 22),
     (128 * 4096, "head", 17), (128 * 4096 + 1, "even", 23), (128 * 4096 + 3, "as_many", 22),
-    (128 * 8192 + 5, "even", 12)])
+    (128 * 8192 + 5, "even", 12)]
+
+
+@pytest.mark.parametrize("n,layout,bits", SIZES)
 def test_grouping_sort(n, layout, bits):
     rng = np.random.default_rng(n + bits)
     lens = _lens(rng, layout, n)
@@ -63,6 +66,45 @@ def test_grouping_sort(n, layout, bits):
             hl.hl_embbag_bwd_grouping(h, cap, nb, 1, n, ws, keys, bags)
             check_grouping(keys.cpu().numpy().view(np.uint32), bags.cpu().numpy().view(np.uint32), codes, bag_of, n_hot,
                            k_cap, f"{layout} {n}")
+        assert hl.hl_last_device_error(h) == 0
+    finally:
+        h.close()
+
+
+@pytest.mark.parametrize("dim,dtype", [(16, "f32"), (64, "f32"), (64, "bf16")])
+@pytest.mark.parametrize("n,layout,bits", SIZES)
+def test_forward_beside_sort(n, layout, bits, dim, dtype):
+    """hl_embbag_fwd_plan where the forward runs beside the sort's passes: bags of
+    any layout, tiles of every size, one to three passes to share the bags among;
+    rows of fewer than 8 lanes and of more.  Pooled outputs bit for bit those of
+    hl_embbag_fwd, the grouping that of hl_embbag_bwd_plan."""
+    rng = np.random.default_rng(n + bits)
+    lens = _lens(rng, layout, n)
+    nb = lens.size
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n_hot, k_cap = 300, 400
+    cap = (1 << bits) - 1 - n_hot
+    h = hl.hl_create(np.array([1000], np.uint32), dim, dtype, k_cap)
+    try:
+        hl.hl_set_hot(h, torch.arange(n_hot, dtype=torch.int32, device="cuda"), n_hot)
+        hot = rng.zipf(1.3, n) % n_hot
+        cold = k_cap + np.where(rng.random(n) < 0.5, rng.integers(0, cap, n), rng.zipf(1.2, n) % cap)
+        dc = torch.from_numpy(np.where(rng.random(n) < 0.6, hot, cold).astype(np.int32)).cuda()
+        dp = torch.from_numpy(ptr).cuda()
+        tt = torch.float32 if dtype == "f32" else torch.bfloat16
+        w, s = (torch.randn((k, dim), device="cuda", dtype=tt) for k in (n_hot, cap))
+        ws = torch.zeros(hl.hl_workspace_bytes(h, n, nb, nb), dtype=torch.uint8, device="cuda")
+        i32 = lambda: torch.zeros(n, dtype=torch.int32, device="cuda")
+        k1, b1, k2, b2 = i32(), i32(), i32(), i32()
+        want, out = (torch.full((nb, dim), v, device="cuda") for v in (7.0, 8.0))
+        hl.hl_embbag_fwd(h, w, s, cap, dc, dp, nb, 1, n, None, None, nb, want)
+        hl.hl_embbag_bwd_plan(h, cap, dc, dp, nb, 1, n, None, None, nb, ws)
+        hl.hl_embbag_bwd_grouping(h, cap, nb, 1, n, ws, k1, b1)
+        for again in range(2):
+            hl.hl_embbag_fwd_plan(h, w, s, cap, dc, dp, nb, 1, n, out, ws)
+            hl.hl_embbag_bwd_grouping(h, cap, nb, 1, n, ws, k2, b2)
+            assert torch.equal(out, want)
+            assert torch.equal(k1, k2) and torch.equal(b1, b2)
         assert hl.hl_last_device_error(h) == 0
     finally:
         h.close()
