@@ -358,63 +358,77 @@ extern "C" hl_status hl_lookup_gids(const hl_handle* h, const uint32_t* rows, co
 }
 
 // ----------------------------------------------------------------------------- counting
-// A block takes CT_THREADS * CT_ITEMS lookups and adds up equal ids in an LDS
-// table first (open addressing, CT_PROBES probes; an id that finds no slot goes
-// to memory directly), then adds each held id's count with one atomic.  The
-// kernel is bound by atomics that meet on one cache line (the popular rows,
-// and every row of a small table): they complete one after another.  So the
-// blocks walk the lookups with stride n_tables, which in the one-lookup-per-bag
-// layout gives a block one table's lookups (any order counts the same): a row
-// then meets about as many atomics as its table has blocks.  212,992 lookups
-// of 26 tables (100 to 4e7 rows, Zipf 1.1): one atomic per lookup 36.8 us, the
-// LDS table over consecutive lookups 18.7, with the stride 8.6 (4.0 of it the
-// loads and the LDS table; 1024 to 4096 lookups per block 8.0 to 11.4).
-// 328,000 lookups of multi-hot bags: 100.5 -> 13.4 us.
-#define CT_THREADS 512
-#define CT_ITEMS 4
-#define CT_SLOTS 4096
+// A block takes THREADS * CT_ITEMS lookups and adds up equal ids in an LDS table
+// first (open addressing, CT_PROBES probes; an id that finds no slot goes to
+// memory directly); the thread that put an id into its slot then adds the slot's
+// count with one atomic.  The kernel is bound by atomics that meet on one cache
+// line (the popular rows, and every row of a small table): they complete one
+// after another.  So the blocks walk the lookups with stride n_tables, which in
+// the one-lookup-per-bag layout gives a block one table's lookups (any order
+// counts the same): a row then meets about as many atomics as its table has
+// blocks.  1024 lookups a block, so that they reach every compute unit; 2048 where
+// 256 such blocks are too few, since then the meetings count.  Back to back, one
+// atomic per lookup, then blocks of 2048 in LDS with every slot looked through at
+// the end, then this: 212,992 lookups of 1e6 rows in 26 tables 49.3, 9.1 and 8.4
+// us (Zipf 1.2) or 9.8, 12.6 and 11.0 (rows of equal weight: the LDS table then
+// finds little to add up), 852,000 (Zipf) 192, 25.3 and 24.2 (blocks of 1024
+// there 28.0).
+#define CT_ITEMS 2
 #define CT_PROBES 4
-__global__ void __launch_bounds__(CT_THREADS)
+#define CT_BLOCKS 256
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
 hl_k_count(const uint32_t* __restrict__ gids, uint32_t n, uint32_t stride, uint32_t* __restrict__ counts,
            uint64_t n_rows, uint32_t* err) {
-  __shared__ uint32_t key[CT_SLOTS], cnt[CT_SLOTS];
-  const uint32_t q0 = blockIdx.x * (CT_THREADS * CT_ITEMS) + threadIdx.x;
+  constexpr int SLOTS = 2 * THREADS * CT_ITEMS;
+  __shared__ uint4 key4[SLOTS / 4], cnt4[SLOTS / 4];
+  uint32_t *key = reinterpret_cast<uint32_t*>(key4), *cnt = reinterpret_cast<uint32_t*>(cnt4);
+  const uint32_t q0 = blockIdx.x * (THREADS * CT_ITEMS) + threadIdx.x;
   // position q of the walk is lookup (q % per) stride + q / per
   const uint32_t per = (n + stride - 1) / stride;
   uint32_t g[CT_ITEMS];
   bool in[CT_ITEMS];
 #pragma unroll
   for (int k = 0; k < CT_ITEMS; ++k) {
-    const uint32_t q = q0 + k * CT_THREADS, t = q / per;
+    const uint32_t q = q0 + k * THREADS, t = q / per;
     const uint64_t i = (uint64_t)(q - t * per) * stride + t;
     in[k] = t < stride && i < n;
     g[k] = in[k] ? gids[i] : 0u;
   }
-  for (int j = threadIdx.x; j < CT_SLOTS; j += CT_THREADS) {
-    key[j] = 0xFFFFFFFFu;  // (no row's id)
-    cnt[j] = 0;
+  for (int j = threadIdx.x; j < SLOTS / 4; j += THREADS) {
+    key4[j] = make_uint4(~0u, ~0u, ~0u, ~0u);  // (no row's id)
+    cnt4[j] = make_uint4(0u, 0u, 0u, 0u);
   }
   __syncthreads();
+  uint32_t slot[CT_ITEMS], old[CT_ITEMS];
+  bool mine[CT_ITEMS];  // this thread put the id into its slot, and adds the slot's count
 #pragma unroll
   for (int k = 0; k < CT_ITEMS; ++k) {
-    if (!in[k]) continue;
-    if (g[k] >= n_rows) {
+    if (in[k] && g[k] >= n_rows) {
       hl_flag(err, HL_DEVERR_OUT_OF_RANGE);
-      continue;
+      in[k] = false;
     }
-    uint32_t slot = hl_cg_hash(g[k]) % CT_SLOTS;
-    bool held = false;
-    for (int p = 0; p < CT_PROBES && !held; ++p) {
-      const uint32_t old = atomicCAS(&key[slot], 0xFFFFFFFFu, g[k]);
-      held = old == 0xFFFFFFFFu || old == g[k];
-      if (!held) slot = (slot + 1) % CT_SLOTS;
+    slot[k] = hl_cg_hash(g[k]) % SLOTS;
+    old[k] = in[k] ? atomicCAS(&key[slot[k]], 0xFFFFFFFFu, g[k]) : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < CT_ITEMS; ++k) {
+    mine[k] = false;
+    if (!in[k]) continue;
+    bool held = old[k] == 0xFFFFFFFFu || old[k] == g[k];
+    for (int p = 1; p < CT_PROBES && !held; ++p) {
+      slot[k] = (slot[k] + 1) % SLOTS;
+      old[k] = atomicCAS(&key[slot[k]], 0xFFFFFFFFu, g[k]);
+      held = old[k] == 0xFFFFFFFFu || old[k] == g[k];
     }
-    if (held) atomicAdd(&cnt[slot], 1u);
+    mine[k] = old[k] == 0xFFFFFFFFu;
+    if (held) atomicAdd(&cnt[slot[k]], 1u);
     else atomicAdd(counts + g[k], 1u);
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < CT_SLOTS; j += CT_THREADS)
-    if (cnt[j]) atomicAdd(counts + key[j], cnt[j]);
+#pragma unroll
+  for (int k = 0; k < CT_ITEMS; ++k)
+    if (mine[k]) atomicAdd(counts + g[k], cnt[slot[k]]);
 }
 
 extern "C" hl_status hl_profile_count(hl_handle* h, const uint32_t* gids, int64_t n, hl_stream stream) {
@@ -427,8 +441,12 @@ extern "C" hl_status hl_profile_count(hl_handle* h, const uint32_t* gids, int64_
     const uint32_t m = (uint32_t)(n - i < most ? n - i : most);
     const uint32_t stride = (uint32_t)h->n_tables < m ? (uint32_t)h->n_tables : m;
     const uint64_t walk = (uint64_t)hl_div_up(m, stride) * stride;
-    HL_KERNEL(h, s, "hl_k_count", hl_k_count, dim3(hl_div_up(walk, CT_THREADS * CT_ITEMS)), dim3(CT_THREADS), 0, s,
-              gids + i, m, stride, h->d_counts, h->n_rows, h->d_err);
+#define CNT(T)                                                                                                     \
+  HL_KERNEL(h, s, "hl_k_count", hl_k_count<T>, dim3(hl_div_up(walk, T * CT_ITEMS)), dim3(T), 0, s, gids + i, m, stride, \
+            h->d_counts, h->n_rows, h->d_err)
+    if (walk <= CT_BLOCKS * 512 * CT_ITEMS) CNT(512);
+    else CNT(1024);
+#undef CNT
   }
   HL_LAUNCHED();
   return HL_OK;

@@ -68,6 +68,31 @@ def test_count_and_topk(n_rows, tables):
         h.close()
 
 
+@pytest.mark.parametrize("n", [1, 1023, 1025, 2049, 262_144, 262_145, 300_001])
+@pytest.mark.parametrize("tables", [1, 7])
+def test_count_block_sizes(n, tables):
+    """Access counting where its blocks change size (256 blocks of 1024 lookups),
+    on one id, a few, and so many that a block's LDS table refuses some; ids that
+    are no row's are reported and not counted."""
+    rng = np.random.default_rng(n + tables)
+    n_rows = 7 * 300_000
+    h = hl.hl_create(np.full(tables, n_rows // tables, np.uint32), 4, "f32", 10)
+    try:
+        cnt = torch.zeros(n_rows, dtype=torch.int32, device="cuda")
+        want = np.zeros(n_rows, np.int64)
+        for wide in (1, 40, n_rows):
+            ids = rng.integers(0, wide, n).astype(np.uint32)
+            if wide == 40:
+                ids[[0, n // 2, n - 1]] = [n_rows, 0xFFFFFFFF, n_rows + 5]
+            hl.hl_profile_count(h, _dev(ids), n)
+            want += np.bincount(ids[ids < n_rows], minlength=n_rows)
+            assert hl.hl_last_device_error(h) == (hl.DEVERR["OUT_OF_RANGE"] if wide == 40 else 0)
+        hl.hl_profile_counts(h, cnt)
+        assert np.array_equal(u32(cnt), want.astype(np.uint32))
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("n_sets,ways,n", [(1, 16, 7), (1, 16, 8), (1, 5, 9), (1, 16, 71), (2, 1, 81), (1, 16, 72),
                                            (1, 16, 137), (3, 16, 5000), (7, 3, 9000), (40, 16, 20011), (300, 2, 3000),
                                            (1, 16, 328), (1, 16, 336), (1, 7, 700)])
