@@ -429,17 +429,19 @@ bw_reduce1(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals,
 // pieces in plain ascending order).
 //
 // A segment by the whole block: its loads that need nothing but the tile index
-// (its key and piece, the next tiles' flags) are issued together, and the row
-// with the pieces of the later tiles.  Nothing is done for one of at most `most`
-// pieces.  Every thread of the block calls it.
+// (its key and piece) are issued together, and the row with the pieces of the
+// later tiles.  a: a tile inside the segment up to which all after t are; f2: the
+// flag of tile a + 1 + this thread; s_end: n_tiles, in LDS, seen by every thread.
+// Nothing is done for one of at most `most` pieces.  Every thread of the block
+// calls it.
 template <int VEC, bool BF, bool SPLIT>
-__device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t most, uint32_t n_tiles, eb_geom g, void* w_hot, void* stg,
+__device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t a, uint32_t f2, uint32_t* s_end, uint32_t most,
+                                                uint32_t n_tiles, eb_geom g, void* w_hot, void* stg,
                                                 uint32_t n_hot, float lr, const float* __restrict__ tfirst,
                                                 const float* __restrict__ tlast, const uint32_t* __restrict__ tflag,
                                                 const uint32_t* __restrict__ tkey, float* __restrict__ gc,
                                                 uint32_t gc_rows) {
   typedef typename RowIO<VEC, BF>::T T;
-  __shared__ uint32_t s_end;
   __shared__ float part[RB_WAVES * 64 * VEC];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int gi = lane / g.G, gl = lane - gi * g.G;
@@ -449,30 +451,40 @@ __device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t most, uint3
   const bool cact = gact && colv < g.vpr;
   const int64_t col = (int64_t)colv * VEC;
   const uint32_t key = tkey[t];
-  const uint32_t t2 = t + 1 + threadIdx.x;
-  const uint32_t f2 = t2 < n_tiles ? tflag[t2] : GF_W;
   float v0[VEC];  // piece 0 (this tile's), summed by group 0
 #pragma unroll
   for (int e = 0; e < VEC; ++e) v0[e] = 0.f;
   if (grp == 0 && cact) ld_f32<VEC>(tlast + (int64_t)t * g.D + col, v0);
-  if (threadIdx.x == 0) s_end = n_tiles;
+  // the first tile after t that is not wholly inside the segment holds its
+  // last piece (a window of RB_BLOCK tiles, then of four times as many; one lane
+  // of a wave lowers s_end, since an LDS atomic goes lane by lane)
+  const uint32_t w64 = (uint32_t)w * 64;
+  const uint64_t m2 = __ballot(!(f2 & GF_W));
+  if (m2 && lane == 0) atomicMin(s_end, a + w64 + (uint32_t)__ffsll((unsigned long long)m2));
   __syncthreads();
+  uint32_t tend = *s_end;
   // the row, for group 0 (its address needs only the key)
   const bool defer = SPLIT && bw_deferred(key, n_hot, gc_rows);
-  float wv[VEC];
+  typename RowIO<VEC, BF>::Raw wr;  // (unpacked when it is used)
   T* rp = bw_row<VEC, BF>(w_hot, stg, n_hot, g.D, key) + col;
-  if (grp == 0 && cact && !defer) RowIO<VEC, BF>::load(rp, wv);
-  // the first tile after t that is not wholly inside the segment holds its
-  // last piece (a window of RB_BLOCK tiles at a time)
-  if (!(f2 & GF_W)) atomicMin(&s_end, t2);
-  __syncthreads();
-  uint32_t tend = s_end;
-  for (uint32_t base = t + 1 + RB_BLOCK; tend == n_tiles && base < n_tiles; base += RB_BLOCK) {
+  if (grp == 0 && cact && !defer) wr = RowIO<VEC, BF>::load_raw(rp);
+  for (uint32_t base = a + 1 + RB_BLOCK; tend == n_tiles && base < n_tiles; base += 4 * RB_BLOCK) {
     __syncthreads();  // (every thread has read s_end before any lowers it)
-    const uint32_t t3 = base + threadIdx.x;
-    if (t3 < n_tiles && !(tflag[t3] & GF_W)) atomicMin(&s_end, t3);
+    uint32_t f3[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t t3 = base + i * RB_BLOCK + threadIdx.x;  // (clamped, not skipped: loads in flight together)
+      f3[i] = tflag[min(t3, n_tiles - 1)] | (t3 < n_tiles ? 0u : GF_W);
+    }
+    uint32_t end = n_tiles;
+#pragma unroll
+    for (int i = 3; i >= 0; --i) {
+      const uint64_t m3 = __ballot(!(f3[i] & GF_W));
+      if (m3) end = base + i * RB_BLOCK + w64 + (uint32_t)__ffsll((unsigned long long)m3) - 1;
+    }
+    if (end < n_tiles && lane == 0) atomicMin(s_end, end);
     __syncthreads();
-    tend = s_end;
+    tend = *s_end;
   }
   const uint32_t npieces = (tend < n_tiles ? tend : n_tiles - 1) - t + 1;
   if (npieces <= most) return;  // (the same for every thread of the block)
@@ -512,6 +524,8 @@ __device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t most, uint3
       st_f32<VEC>(gc + (int64_t)(key - n_hot) * g.D + col, acc);
       return;
     }
+    float wv[VEC];
+    RowIO<VEC, BF>::unpack(wr, wv);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) wv[e] -= lr * acc[e];
     RowIO<VEC, BF>::store(rp, wv);
@@ -529,7 +543,10 @@ __device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t most, uint3
 // with three barriers before its store, took 7.5 us for 4,438 tiles and 13.4 for
 // 17,750 (f32 rows of 64), 9.2 for 6,828 with a run over 150 of them (bf16 rows
 // of 128); 5.4, 7.5 and 8.7 like this (the long ones one after another in the
-// blocks that met them: 5.8, 8.2 and 10.4).
+// blocks that met them: 5.8, 8.2 and 10.4).  One row over 5,200 tiles (f32 rows of
+// 64) 80.4 us with a block per tile, 83.5 with the search and one window of flags
+// after another, 74.4 like this; 328,000 lookups of Zipf 1.2 (bf16 rows of 128, one
+// row over 1,200 tiles) 25.7, 26.8 and 24.6.
 #define R2_SHORT 8
 // blocks that look for long segments, and all blocks, for n_tiles tiles (at
 // least two row groups to a block: RB_WAVES)
@@ -561,13 +578,19 @@ __device__ __forceinline__ void bw_reduce2_body(uint32_t bid, uint32_t n_tiles, 
     uint32_t fb[R2_SHORT];  // flags of tiles a, a - 1, ..., a - step
 #pragma unroll
     for (int i = 0; i < R2_SHORT; ++i) fb[i] = tflag[a - min((uint32_t)i, step)];
+    // (the next tiles' flags in the same round, for a segment that goes on)
+    const uint32_t t2 = a + 1 + threadIdx.x;
+    const uint32_t f2 = tflag[min(t2, n_tiles - 1)] | (t2 < n_tiles ? 0u : GF_W);
+    __shared__ uint32_t s_end;
+    if (threadIdx.x == 0) s_end = n_tiles;
+    __syncthreads();
     if (!(fb[0] & GF_W)) return;
     uint32_t back = 0;  // the segment's start, if no earlier looked-at tile is inside it
 #pragma unroll
     for (int i = R2_SHORT - 1; i > 0; --i)
       if (i <= (int)step && !(fb[i] & GF_W)) back = i;
     if (back != 0)
-      bw_reduce2_long<VEC, BF, SPLIT>(a - back, most, n_tiles, g, w_hot, stg, n_hot, lr, tfirst, tlast, tflag, tkey, gc,
+      bw_reduce2_long<VEC, BF, SPLIT>(a - back, a, f2, &s_end, most, n_tiles, g, w_hot, stg, n_hot, lr, tfirst, tlast, tflag, tkey, gc,
                                       gc_rows);
     return;
   }
