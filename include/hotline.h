@@ -324,10 +324,10 @@ hl_status hl_embbag_bwd_sgd(hl_handle* h, void* w_hot, void* staging, int32_t st
  * until the process ends (hl_create looks up its address on the handle's
  * device and zero-fills it once).  The call allocates nothing.  Mini-batches
  * whose plan needs more than the array (about 50 bytes per lookup at dim 64,
- * 85 at dim 128: each of the benchmark's mini-batches fits) return HL_ERR_CAPACITY and enqueue nothing.  Every call
- * on one GPU shares that GPU's array and leaves its last contents there: calls
- * that overlap on one GPU (on concurrent streams or host threads) race and
- * must not be issued. */
+ * 82 at dim 128: each of the benchmark's mini-batches fits) return
+ * HL_ERR_CAPACITY and enqueue nothing.  Every call on one GPU shares that GPU's
+ * array and leaves its last contents there: calls that overlap on one GPU (on
+ * concurrent streams or host threads) race and must not be issued. */
 size_t hl_noalloc_scratch_bytes(void);
 hl_status hl_embbag_bwd_sgd_noalloc(hl_handle* h, void* w_hot, void* staging, int32_t staging_rows,
                                     const int32_t* codes, const int32_t* bag_ptr, int32_t n_samples,
@@ -359,9 +359,11 @@ hl_status hl_embbag_bwd_apply(hl_handle* h, void* w_hot, void* staging, int32_t 
  * sample, with the same results (out bit for bit, the same grouping left in
  * the workspace for hl_embbag_bwd_apply).  The backward's grouping reads only
  * the codes (Sec. IV: hot rows are updated on the GPU after both forwards),
- * so for a one-hot mini-batch (one lookup per bag, grouped table by table)
- * the sorts of the tables run in the forward's launch, on compute units the
- * forward leaves free; other mini-batches take the two calls in turn.
+ * so for a one-hot mini-batch (one lookup per bag, grouped table by table;
+ * rows of 4 elements per lane) the sorts of the tables run in the forward's
+ * launch, on compute units the forward leaves free, and for other mini-batches
+ * (rows of 16-byte lane loads) the forward runs in the launches of the general
+ * sort's passes.  Rows of other widths take the two calls in turn.
  * Arguments as those two calls; the workspace as hl_embbag_bwd_plan's. */
 hl_status hl_embbag_fwd_plan(hl_handle* h, const void* w_hot, const void* staging, int32_t staging_rows,
                              const int32_t* codes, const int32_t* bag_ptr, int32_t n_samples,

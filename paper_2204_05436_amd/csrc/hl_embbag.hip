@@ -1120,11 +1120,16 @@ static int eb_device_cus(const hl_handle* h) {
 }
 
 // Lookups per table up to which the sorts beside the forward read the codes
-// themselves: each lane's code is a cache line of its own, which a block's
-// compute unit takes one a cycle, while the forward keeps the memory busy.
-// gt_prep and the launch, then the launch alone: 1024 per table (8 tables, rows
-// of 16) 4.2 + 10.7 us, 10.1; 4096 (26 tables, rows of 16) 5.6 + 13.1, 15.8;
-// 8192 (26 tables, rows of 64) 5.6 + 20.1, 32.7.
+// themselves, which spares gt_prep's launch.  A lane's code lies T codes from its
+// neighbour's, from 32 tables on in a cache line of its own, and a compute unit
+// takes one line a cycle; but the line lies where the sort goes from 4 to 8 items
+// per thread and its registers no longer fit (with 8, 62 spilled at any number of
+// tables; gt_prep's keys need no spills).  Back to back, gt_prep and the launch, then the
+// launch alone, at 4096 lookups per table of 2, 8, 26 and 64 tables: rows of 16
+// 15.4, 15.7, 17.5, 19.9 us and 13.7, 14.0, 14.6, 16.2; rows of 64 15.4, 16.2, 17.9,
+// 29.3 and 13.7, 14.5, 15.2, 23.5.  At 8192 of 1, 8, 26 and 64 tables, rows of 16:
+// 21.1, 21.9, 23.5, 26.3 and 24.5, 26.9, 29.8, 37.2 (6000: 19.6, 20.1, 21.8, 24.5 and
+// 23.0, 24.7, 26.7, 31.0).
 #define GT_CODES_E 4096
 template <int VEC, bool BF>
 static void launch_fwd_gt(hl_handle* h, hipStream_t s, const void* w_hot, const void* stg, int32_t stg_rows,

@@ -4,7 +4,7 @@
 // cannot allocate device memory (code under graph capture, serving loops,
 // harnesses that forbid allocation).  Every call on a GPU uses that GPU's copy
 // and leaves its last contents there; the kernels keep the state that must
-// start at zero (tile counters, look-back words) reset themselves, and the
+// start at zero (counters, tickets, published words) reset themselves, and the
 // copy is zero-filled once when its address is looked up.  Calls that overlap
 // on one GPU race on the array.
 #include <mutex>

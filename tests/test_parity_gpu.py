@@ -127,10 +127,11 @@ def test_backward_key_widths(bits):
     parity_case(w, batches=([], mb), hot_ids=hot, split=bits % 2 == 0, staging_cap=cap)
 
 
-@pytest.mark.parametrize("n", [2048 * 128, 2048 * 128 + 1, 3072 * 128, 3072 * 128 + 1])
+@pytest.mark.parametrize("n", [1024 * 128, 1024 * 128 + 1, 2048 * 128, 2048 * 128 + 1, 3072 * 128 + 1, 4096 * 128,
+                               4096 * 128 + 1])
 def test_sort_tile_sizes(n):
-    """The general radix sort takes 4, 6 or 12 items per thread of its
-    512-thread tiles, the fewest that keep a sort to 128 tiles: mini-batches of
+    """The general radix sort takes 1, 2, 4 or 8 items per thread of its
+    1024-thread tiles, the fewest that keep a sort to 128 tiles: mini-batches of
     exactly n lookups on either side of each switch, in multi-hot bags (so the
     grouping by table does not apply), against the oracle (the grouping
     against the stable order of the keys)."""
@@ -336,8 +337,8 @@ def test_plan_apply_contract():
                                          (1_300_000, 1, 1), (60_000, 26, 1)])
 def test_dispatch_shapes(B, T, max_len):
     """The dispatch kernel against the oracle's ids, classify, partition and remap:
-    one tile to ~2000 tiles, ragged tails, multi-hot bags, and sizes beyond its
-    look-back state (which take the four calls in turn); three calls in a row
+    one tile to several hundred, ragged tails and multi-hot bags (the sizes where
+    its blocks change: test_dispatch_gpu.py); three calls in a row
     (the device-side epoch advances)."""
     import oracle as O
     rng = np.random.default_rng(B + T)
