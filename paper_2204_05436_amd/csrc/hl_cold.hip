@@ -6,7 +6,8 @@
 //   insert : each cold lookup (code -1) of a selected sample enters an
 //            open-addressing hash table keyed by row id with one CAS (a 64-bit
 //            atomic min keeps the smallest lookup index per id); a thread per
-//            lookup, or with a sample list a wave or a block per listed sample
+//            lookup, or with a sample list 8 to 256 threads per listed sample
+//            (a long one by whole blocks)
 //   rank   : a scan over all lookups in index order (tiles of 2048, their counts
 //            published and read by the whole block) numbers the first
 //            occurrences: staging row u of each id

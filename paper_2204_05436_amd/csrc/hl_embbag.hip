@@ -545,8 +545,9 @@ __device__ __forceinline__ void bw_reduce2_long(uint32_t t, uint32_t a, uint32_t
 // of 128); 5.4, 7.5 and 8.7 like this (the long ones one after another in the
 // blocks that met them: 5.8, 8.2 and 10.4).  One row over 5,200 tiles (f32 rows of
 // 64) 80.4 us with a block per tile, 83.5 with the search and one window of flags
-// after another, 74.4 like this; 328,000 lookups of Zipf 1.2 (bf16 rows of 128, one
-// row over 1,200 tiles) 25.7, 26.8 and 24.6.
+// after another, 74.4 with the next flags loaded beside the search and four windows
+// at a time after that; 328,000 lookups of Zipf 1.2 (bf16 rows of 128, one row over
+// 1,200 tiles) 25.7, 26.8 and 24.6, and the 5.4 and 8.7 above 4.7 and 7.0.
 #define R2_SHORT 8
 // blocks that look for long segments, and all blocks, for n_tiles tiles (at
 // least two row groups to a block: RB_WAVES)

@@ -1,6 +1,6 @@
 """The cold plan's selections against the oracle: every sample, the first ones,
-a list of samples (a wave or a block each; out of order, repeated, counted on
-the device), and enough lookups that the rank scan goes back to a look-back."""
+a list of samples (8 to 256 threads or whole blocks each; out of order,
+repeated, counted on the device), and enough lookups that the rank scan goes back to a look-back."""
 import numpy as np
 import pytest
 import torch
