@@ -491,13 +491,19 @@ ds_kernel(const uint32_t* __restrict__ rows, const int32_t* __restrict__ bag_ptr
 // lookups took 12.7 us with about 64 or 96 blocks aimed at, 11.8 with 128, 11.5
 // with 160, 12.0 with 192, 12.3 with 256 (15.0 with 104 blocks, a look-back
 // through inclusive prefixes and a second counter for the call's end); batch
-// 32768 26.9 -> 20.5 with 208 blocks of 4096 lookups (416 of 2048: 22.4).  About
+// 32768 26.9 -> 20.5 with 208 blocks of 4096 lookups (416 of 2048: 22.4).  Back to
+// back with about 64, 160 and 256: 106,496 lookups of 26 tables 10.3, 10.1, 10.3;
+// 425,984 15.1, 13.8, 13.3; 1.7 million 26.8, 26.8, 36.2; 328,000 in bags of 20
+// 12.3, 11.2, 11.2; 1.3 million 20.5, 20.5, 25.0.  About
 // 64 on a stream of few compute units (cus), where more blocks only queue, while
 // their published words have room; past that as on a wide stream, so whether the
 // dispatch is fused does not depend on the stream (the wide sizing has room
-// wherever the other has: fewer, larger blocks, and the same caps).
+// wherever the other has: fewer, larger blocks, and the same caps).  cus() is asked
+// only where the two differ (reading a stream's mask costs a small dispatch a tenth
+// of its time).
+template <typename F>
 static int64_t ds_spb(const hl_handle* h, int32_t n_samples, int32_t bps, int64_t n_lookups, const void* workspace,
-                      size_t ws_bytes, int cus) {
+                      size_t ws_bytes, F cus) {
   if (n_samples == 0 || bps > DS_MAX_BAGS || h->n_tables > DS_MAX_TABLES || !workspace || ws_bytes < HL_WS_HEADER)
     return 0;
   auto sized = [&](int64_t aim, int64_t most) {  // 0: more blocks than words
@@ -506,13 +512,13 @@ static int64_t ds_spb(const hl_handle* h, int32_t n_samples, int32_t bps, int64_
     spb = std::max<int64_t>(std::min<int64_t>({spb, DS_MAX_BAGS / bps, DS_MAX_SPB}), 1);
     return (n_samples + spb - 1) / spb <= HL_DISP_MAX_TILES ? spb : 0;
   };
-  const int64_t spb = cus > DS_BLOCKS_WIDE ? 0 : sized(DS_BLOCKS_AIM, DS_LOOKUPS_MAX);
-  return spb ? spb : sized(DS_BLOCKS_WIDE, 2 * DS_LOOKUPS_MAX);
+  const int64_t wide = sized(DS_BLOCKS_WIDE, 2 * DS_LOOKUPS_MAX), spb = sized(DS_BLOCKS_AIM, DS_LOOKUPS_MAX);
+  return spb == 0 || spb == wide || cus() > DS_BLOCKS_WIDE ? wide : spb;
 }
 
 bool hl_dispatch_fused(const hl_handle* h, int32_t n_samples, int32_t bps, int64_t n_lookups, const void* workspace,
                        size_t ws_bytes) {
-  return h && bps >= 1 && n_samples >= 0 && ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes, 0) > 0;
+  return h && bps >= 1 && n_samples >= 0 && ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes, [] { return 0; }) > 0;
 }
 
 extern "C" hl_status hl_dispatch(hl_handle* h, const uint32_t* rows, const int32_t* bag_ptr, int32_t n_samples,
@@ -532,7 +538,7 @@ hl_status hl_dispatch_ex(hl_handle* h, const uint32_t* rows, const int32_t* bag_
   if (n_lookups > 0 && (!rows || !gids || !codes)) return HL_ERR_INVALID_ARG;
   if ((int64_t)n_samples * bps >= (1ll << 31) || n_lookups >= (1ll << 31)) return HL_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  const int64_t spb = ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes, hl_stream_cus(s));
+  const int64_t spb = ds_spb(h, n_samples, bps, n_lookups, workspace, ws_bytes, [&] { return hl_stream_cus(h, s); });
   const int64_t tiles = spb ? (n_samples + spb - 1) / spb : 0;
   if (!spb && cf && cf->table) return HL_ERR_INVALID_ARG;  // the fused plan needs the fused dispatch
   if (!spb) {

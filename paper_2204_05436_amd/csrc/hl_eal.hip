@@ -67,7 +67,9 @@ struct eal_rr {
 // us without the long runs) and by the longest run: a popular row gives its set
 // two thousand.  212,992 accesses on 26,436 sets of 16: 634 us with a thread per
 // run; 22 with the first 8 accesses by a thread; 15.5 like this (EAL_SHORT 8, 12,
-// 16: 15.5, 15.8, 16.4).
+// 16: 15.5, 15.8, 16.4).  Whole calls with 4, 8, 12 and 16, Zipf 1.1: 212,992
+// accesses 86.1, 86.8, 86.6, 87.8; a million 324, 324, 324, 327; ids of equal
+// weight, which give no set a long run: 39.5, 36.0, 35.1, 34.8 and 125, 119, 112, 105.
 #define EAL_THREADS 256
 #define EAL_SHORT 8
 #define EAL_AHEAD 4  // times 64 accesses of a long run loaded at once

@@ -1108,18 +1108,6 @@ hl_sort_side_fn hl_fwd_sort_side(bool bf16, int vec) {
   return vec == 4 ? hl_fwd_sort_f32() : nullptr;
 }
 
-// Compute units of the handle's device.
-static int eb_device_cus(const hl_handle* h) {
-  static int cus[64];
-  const int d = h->device >= 0 && h->device < 64 ? h->device : 0;
-  if (cus[d] <= 0) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || v <= 0) v = 1;
-    cus[d] = v;
-  }
-  return cus[d];
-}
-
 // Lookups per table up to which the sorts beside the forward read the codes
 // themselves, which spares gt_prep's launch.  A lane's code lies T codes from its
 // neighbour's, from 32 tables on in a cache line of its own, and a compute unit
@@ -1141,7 +1129,7 @@ static void launch_fwd_gt(hl_handle* h, hipStream_t s, const void* w_hot, const 
   const uint32_t E = (uint32_t)(n_bags / T);
   // one block per compute unit (each holds the sort's LDS): the tables' sorts
   // and, on the other units, the forward
-  const int cus = eb_device_cus(h);
+  const int cus = hl_device_cus(h);
   const uint32_t nf = (uint32_t)std::max(cus > 2 * T ? cus - T : cus, GT_CHECKS);
   const hl_hook hk = hl_hook_take(h);
   gt_src src{};

@@ -457,8 +457,10 @@ __device__ __forceinline__ uint32_t hl_set_of(uint32_t g, uint32_t n_sets) {
   x ^= x >> 16;
   return g == 0xFFFFFFFFu ? n_sets : x % n_sets;
 }
-// Compute units in a stream's mask (0 if it cannot be read).
-int hl_stream_cus(hipStream_t s);
+// Compute units of the handle's device, and in a stream's mask (0 if it cannot be
+// read).
+int hl_device_cus(const hl_handle* h);
+int hl_stream_cus(const hl_handle* h, hipStream_t s);
 
 // Decoupled look-back helpers (epoch-tagged 64-bit status words).  A status
 // word carries its own value, so relaxed agent-scope atomics suffice: no other

@@ -38,6 +38,7 @@
 // 13.3 + 11.2 (852,000 pairs, 11-bit digits: 19.3 + 34.7 + 34.7, now 6.4 + 23.6 +
 // 17.6; 64,500 pairs, 9-bit: 6.6 + 11.6 + 11.6, now 3.5 + 7.5 + 7.6).
 #include <algorithm>
+#include <atomic>
 
 #include "hl_sort_pass.h"
 
@@ -160,7 +161,20 @@ void hl_sort_result(const hl_sort_ws& ws, int bits, uint32_t** out_k, uint32_t**
   *out_v = odd ? ws.v1 : ws.v0;
 }
 
-int hl_stream_cus(hipStream_t s) {
+int hl_device_cus(const hl_handle* h) {
+  static std::atomic<int> cus[64];
+  const int d = h->device >= 0 && h->device < 64 ? h->device : 0;
+  int v = cus[d].load(std::memory_order_relaxed);
+  if (v <= 0) {
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || v <= 0) v = 1;
+    cus[d].store(v, std::memory_order_relaxed);
+  }
+  return v;
+}
+
+// (reading a mask costs the host most of a microsecond; the default stream has none)
+int hl_stream_cus(const hl_handle* h, hipStream_t s) {
+  if (!s) return hl_device_cus(h);
   uint32_t m[16] = {0};
   if (hipExtStreamGetCUMask(s, 16, m) != hipSuccess) return 0;
   int c = 0;
@@ -194,7 +208,7 @@ static hl_status srt_run(hl_handle* h, hl_sort_ws& ws, const hl_sort_src& src, c
   if (n_host > ws.n_max || n_host >= (1u << 30)) return HL_ERR_CAPACITY;
   if (bits > 32) return HL_ERR_UNSUPPORTED;
   const srt_plan pl = srt_make_plan(bits);
-  const int cus = hl_stream_cus(s), items = srt_items(n_host, cus);
+  const int cus = hl_stream_cus(h, s), items = srt_items(n_host, cus);
   const hl_hook hk = hl_hook_take(h);
   const uint32_t tile = (uint32_t)(HL_SORT_THREADS * items), tiles = hl_div_up(n_host, tile);
 #define CNT(NB)                                                                                                      \
